@@ -16,6 +16,7 @@
 
 #include "noble.h"
 #include "noble_gemm_dma.hpp"
+#include "noble_gemm_tile.hpp"
 #include "noble_init.hpp"
 #include "noble_kernels.hpp"
 #include "noble_skinny.hpp"
@@ -284,24 +285,55 @@ int64_t max_gemm_blocks(const noble_linear_desc* d) {
 // (gemm_bf16_kernel), which takes about half the MFMA time of a full tile.
 bool kpair_tile(int tile, int64_t M, bool bsum) { return tile == 256 && M <= 128 && !bsum; }
 
-// A bf16 launch of 256 x 256 tiles that fills its last wave of 256 CUs
-// poorly runs as 256 x 128 `npair` tiles (gemm_bf16_kernel): chosen when
-// their waves, weighted by kHalfTileCost, are fewer.  A half tile does half
-// the MFMA work but loads three quarters of the operand bytes per chunk;
-// measured on the 250M and ViT layers it costs about 0.8 of a full tile
-// (so 2 waves of full tiles beat 3 of half tiles, 1 of half tiles beats 1 of
-// full ones).
-constexpr double kHalfTileCost = 0.8;
-bool npair_pays(int64_t full_blocks, int64_t half_blocks) {
-    const int64_t wf = (full_blocks + 255) / 256, wh = (half_blocks + 255) / 256;
-    return half_blocks < (1 << 22) && (double)wh * kHalfTileCost < 0.95 * (double)wf;
+// Output tiles of the bf16 products y and dx.  256 x 256 (gemm_bf16_kernel)
+// loads the fewest operand bytes per FLOP and wins wherever its tiles fill
+// the 256 CUs; a launch that leaves CUs idle in its only or last wave runs
+// smaller tiles (gemm_tile_kernel).  Measured times fit, per wave of
+// workgroups, chunks x c + e us (a chunk: 64 of K; e: first loads, output);
+// a wave of at most ~60% of the slots runs faster (less traffic at once):
+//   tile       slots   c, e of a full wave    c, e of a part wave
+//   256 x 256   256      1.50, 11               1.36, 10
+//   256 x 128   256      0.95,  6               0.75,  6
+//   128 x 128   256      0.60,  5               0.57,  5
+//    64 x 128   512      0.63,  5               0.45,  5
+// (8192 x 2048 x 2176: 63 / 77 / 102 / 100 us; 2000 x 2048 x 2304: 51 / 34 /
+// 29 / 29 us; 25216 x 768 x 3104: 153 / 148 / 171 / 171 us.)
+enum TileId { kTile256 = 0, kTile256x128, kTile128, kTile64x128, kTileIds };
+struct TileCost {
+    int bm, bn, slots;
+    double c_full, e_full, c_part, e_part;
+};
+constexpr TileCost kTileCost[kTileIds] = {{256, 256, 256, 1.50, 11.0, 1.36, 10.0},
+                                          {256, 128, 256, 0.95, 6.0, 0.75, 6.0},
+                                          {128, 128, 256, 0.60, 5.0, 0.57, 5.0},
+                                          {64, 128, 512, 0.63, 5.0, 0.45, 5.0}};
+double tile_time(const TileCost& t, int64_t blocks, int nk) {
+    const int64_t full = blocks / t.slots, rem = blocks % t.slots;
+    const double f = nk * t.c_full + t.e_full, p = nk * t.c_part + t.e_part;
+    return (double)full * f + (rem == 0 ? 0.0 : (rem * 10 <= t.slots * 6 ? p : f));
+}
+// The tile of G problems [M, N] with nk K chunks (see kTileCost).
+TileId pick_tile(int64_t G, int64_t M, int64_t N, int nk) {
+    TileId best = kTile256;
+    double bt = 0;
+    for (int i = 0; i < kTileIds; ++i) {
+        const TileCost& t = kTileCost[i];
+        const int64_t blocks = G * ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        if (i > 0 && blocks >= (1 << 22)) continue;   // the dispatch limit is checked for 256 x 256
+        const double tt = tile_time(t, blocks, nk);
+        if (i == 0 || tt < bt) {
+            bt = tt;
+            best = (TileId)i;
+        }
+    }
+    return best;
 }
 
+template <typename List>
 struct Batch {
-    GemmBatch b{};
+    List b{};
     int blocks = 0;
-    int tile = 256;      // square output tile
-    bool npair = false;  // bf16: 256 x 128 tiles (set before adding problems)
+    int bm = 256, bn = 256;   // output tile
     // With `partials`, each of the `split` pieces stores its float32 partial
     // [M][ldc] at partials + piece * M * ldc (also for split = 1); without,
     // split > 1 pieces add atomically into C.
@@ -319,14 +351,13 @@ struct Batch {
         p.N = N;
         p.nk = nk;
         p.split = split;
-        p.tiles_m = cdiv(M, tile);
-        p.tiles_n = cdiv(N, npair ? tile / 2 : tile);
+        p.tiles_m = cdiv(M, bm);
+        p.tiles_n = cdiv(N, bn);
         p.tile_begin = blocks;
         p.nblocks = p.tiles_m * p.tiles_n * split;
         p.out_f32 = out_f32 ? 1 : 0;
         p.atomic = split > 1 && !partials ? 1 : 0;
-        p.npair = npair ? 1 : 0;
-        p.kpair = !npair && kpair_tile(tile, M, bsum != nullptr) ? 1 : 0;
+        p.kpair = kpair_tile(bm, M, bsum != nullptr) ? 1 : 0;
         blocks += p.nblocks;
     }
 };
@@ -523,24 +554,55 @@ noble_status check_grids(const noble_linear_desc* d) {
     const int64_t hl = hilo(d);
     const int64_t wgrad =
         tiles(din, dout) + (r > 0 ? tiles(din, hl * R) + G * (tiles(r, dog) + n_mix(d) * tiles(hl * r, hl * r)) : 0);
-    // (an npair launch is chosen only when it has fewer weighted waves: at
-    // most about twice the blocks of a launch of a few waves)
     return std::max({fwd, dx, wgrad}) <= max_gemm_blocks(d) ? NOBLE_OK : NOBLE_ERR_BAD_SHAPE;
 }
 
-// `plain`: the r = 0 forward, launched under its own kernel symbol so that
-// profiles can tell it from the K-extended forward.
-template <typename E, bool AK, bool BKM>
-noble_status launch_gemm(const Batch& bt, hipStream_t st, bool plain = false) {
+// Weight gradients: one grouped launch, A and B both MN-major.
+template <typename E>
+noble_status launch_wgrad(const Batch<GemmBatch>& bt, hipStream_t st) {
+    if constexpr (sizeof(E) == 2)
+        return launch(gemm_bf16_kernel<false, false, true, 0, GemmBatch>, dim3(bt.blocks), dim3(kDmaThreads), st, bt.b);
+    else
+        return launch(gemm_kernel<E, gemm_tile<E>(), gemm_tile<E>(), false, false, true, GemmBatch>, dim3(bt.blocks),
+                      dim3(kThreads), st, bt.b);
+}
+
+// y (BKM = false) or dx (BKM = true) on the tile that its batch was built
+// for.  `plain`: the r = 0 forward, launched under its own kernel symbol so
+// that profiles can tell it from the K-extended forward.
+template <typename E, bool BKM>
+noble_status launch_dense(const Batch<DenseBatch>& bt, TileId tile, hipStream_t st, bool plain = false) {
+    using B = DenseBatch;
     if (bt.blocks == 0) return NOBLE_OK;
     if constexpr (sizeof(E) == 2) {
-        if (AK && !BKM && plain)
-            return launch(gemm_bf16_kernel<AK, BKM, false, 1>, dim3(bt.blocks), dim3(kDmaThreads), st, bt.b);
-        return launch(gemm_bf16_kernel<AK, BKM, !AK && !BKM, 0>, dim3(bt.blocks), dim3(kDmaThreads), st, bt.b);
+        const dim3 grid(bt.blocks);
+        switch (tile) {
+            case kTile256x128:
+                return launch(gemm_tile_kernel<true, BKM, 4, 2, 2, 2, 3, false, B>, grid, dim3(512), st, bt.b);
+            case kTile128:
+                return launch(gemm_tile_kernel<true, BKM, 2, 2, 2, 2, 3, false, B>, grid, dim3(256), st, bt.b);
+            case kTile64x128:
+                return launch(gemm_tile_kernel<true, BKM, 2, 2, 1, 2, 3, false, B>, grid, dim3(256), st, bt.b);
+            default: break;
+        }
+        if (!BKM && plain)
+            return launch(gemm_bf16_kernel<true, BKM, false, 1, B>, grid, dim3(kDmaThreads), st, bt.b);
+        return launch(gemm_bf16_kernel<true, BKM, false, 0, B>, grid, dim3(kDmaThreads), st, bt.b);
     } else {
-        return launch(gemm_kernel<E, gemm_tile<E>(), gemm_tile<E>(), AK, BKM, !AK && !BKM>, dim3(bt.blocks),
+        return launch(gemm_kernel<E, gemm_tile<E>(), gemm_tile<E>(), true, BKM, false, B>, dim3(bt.blocks),
                       dim3(kThreads), st, bt.b);
     }
+}
+
+// Empty batch for y or dx, G problems [M, N] of nk chunks each.
+template <typename E>
+Batch<DenseBatch> dense_batch(int64_t G, int64_t M, int64_t N, int nk, TileId& tile) {
+    Batch<DenseBatch> bt;
+    tile = kTile256;
+    if (sizeof(E) == 2) tile = pick_tile(G, M, N, nk);
+    bt.bm = sizeof(E) == 2 ? kTileCost[tile].bm : gemm_tile<E>();
+    bt.bn = sizeof(E) == 2 ? kTileCost[tile].bn : gemm_tile<E>();
+    return bt;
 }
 
 // float32 path: chain kernels with their own rank projection, one launch per
@@ -741,10 +803,8 @@ noble_status fwd_impl(const noble_linear_desc* d, const void* x, const void* W, 
     constexpr int GBK = gemm_bk<E>();
     const int nk1 = cdiv(din, GBK);
     const int nk = nk1 + (r > 0 ? cdiv(r, GBK) : 0);
-    Batch bt;
-    bt.tile = gemm_tile<E>();
-    if (sizeof(E) == 2)
-        bt.npair = npair_pays((int64_t)G * cdiv(T, 256) * cdiv(dog, 256), (int64_t)G * cdiv(T, 256) * cdiv(dog, 128));
+    TileId tile;
+    Batch<DenseBatch> bt = dense_batch<E>(G, T, dog, nk, tile);
     for (int g = 0; g < G; ++g) {
         const E* Wg = static_cast<const E*>(W) + g * dog;
         const char* C2g = C2s + g * r * (int64_t)ES;
@@ -753,7 +813,7 @@ noble_status fwd_impl(const noble_linear_desc* d, const void* x, const void* W, 
                (int)T, (int)dog, nk, static_cast<E*>(y) + g * dog, dout, sizeof(E) == 4, b ? b + g * dog : nullptr,
                nullptr, 1);
     }
-    return launch_gemm<E, true, false>(bt, st, r == 0 && G == 1);
+    return launch_dense<E, false>(bt, tile, st, r == 0 && G == 1);
 }
 
 template <typename E>
@@ -874,12 +934,11 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
     {
         const int nk1 = cdiv(dout, GBK);
         const int nk = nk1 + (r > 0 ? cdiv(R, GBK) : 0);
-        Batch bt;
-        bt.tile = gemm_tile<E>();
-        if (sizeof(E) == 2) bt.npair = npair_pays((int64_t)cdiv(T, 256) * cdiv(din, 256), (int64_t)cdiv(T, 256) * cdiv(din, 128));
+        TileId tile;
+        Batch<DenseBatch> bt = dense_batch<E>(1, T, din, nk, tile);
         bt.add(operand2(seg(dy, dout, dout), seg(dHs, hl * R, R), nk1, T), operand2(seg(W, dout, dout), seg(Wd, R, R), nk1, din),
                (int)T, (int)din, nk, dx, din, sizeof(E) == 4, nullptr, nullptr, 1);
-        NOBLE_TRY((launch_gemm<E, true, true>(bt, st)));
+        NOBLE_TRY((launch_dense<E, true>(bt, tile, st)));
     }
 
     // Weight gradients, reduced over tokens (K = T), A and B both MN-major, in
@@ -900,8 +959,8 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
             red.fold[red.count] = fold;
             ++red.count;
         };
-        Batch bt;
-        bt.tile = gemm_tile<E>();
+        Batch<GemmBatch> bt;
+        bt.bm = bt.bn = gemm_tile<E>();
         const Operand xT = operand1(seg(x, din, T), din);
         const Operand dyN = operand1(seg(dy, dout, T), dout);
         bt.add(xT, dyN, (int)din, (int)dout, nkT, dW, dout, true, nullptr, db, wp.split,
@@ -951,7 +1010,7 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
         t_wgrad_ev0 = t_wgrad_ev1 = nullptr;
         t_wgrad_wgs = nullptr;
         if (ev0 && hipEventRecord(ev0, st) != hipSuccess) return NOBLE_ERR_HIP;
-        NOBLE_TRY((launch_gemm<E, false, false>(bt, st)));
+        NOBLE_TRY(launch_wgrad<E>(bt, st));
         if (ev1 && hipEventRecord(ev1, st) != hipSuccess) return NOBLE_ERR_HIP;
         if (copies) {
             const int64_t arr = (int64_t)kChainCopies * R;

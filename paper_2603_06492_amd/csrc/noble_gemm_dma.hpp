@@ -161,8 +161,8 @@ constexpr int kStoreNT = 2;
 
 // TAG only separates launch sites in profiles (1: the plain r = 0 forward);
 // the code is the same.
-template <bool AK, bool BKM, bool HAS_BSUM, int TAG>
-__global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(GemmBatch batch) {
+template <bool AK, bool BKM, bool HAS_BSUM, int TAG, typename Batch>
+__global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(Batch batch) {
     constexpr int BM = 256, BN = 256, NW = kDmaWM * kDmaWN;
     constexpr int WTM = BM / kDmaWM, WTN = BN / kDmaWN;   // wave tile 128 x 64
     constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(GemmBatch bat
     const int bid = blockIdx.x;
     int q = 0;
 #pragma unroll
-    for (int t = 1; t < kMaxProblems; ++t)
+    for (int t = 1; t < Batch::kMax; ++t)
         if (t < batch.count && bid >= batch.p[t].tile_begin) q = t;
     const GemmProblem& P = batch.p[q];
 
@@ -190,8 +190,8 @@ __global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(GemmBatch bat
     const int first_m = grp * kGroupM;
     const int gsz = min(P.tiles_m - first_m, kGroupM);
     const int tm = first_m + in % gsz, tn = in / gsz;
-    const bool kpair = P.kpair != 0, npair = P.npair != 0;
-    const int m0 = tm * BM, n0 = tn * (npair ? BN / 2 : BN);
+    const bool kpair = P.kpair != 0;
+    const int m0 = tm * BM, n0 = tn * BN;
     const int kc0 = (int)((int64_t)P.nk * piece / P.split);
     const int kc1 = (int)((int64_t)P.nk * (piece + 1) / P.split);
 
@@ -206,15 +206,11 @@ __global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(GemmBatch bat
     // both halves the rows 0..127: half w / 4 takes K steps 2 (w / 4) and
     // 2 (w / 4) + 1 of every chunk, and the second half's sums are added to
     // the first's through LDS at the end, so the half-empty tile costs about
-    // half the MFMA time.  `npair` tiles are 256 x 128 (twice the tiles of a
-    // launch that would under-fill the CUs): the wave that would take N
-    // quarter q >= 2 takes quarter q - 2 and K steps 2 and 3, its partner
-    // (same M half, quarter q - 2) steps 0 and 1, with the same hand-over.
+    // half the MFMA time.
     const int khalf = wave / kDmaWN;
     const int qw = (wave % kDmaWN) ^ (khalf * (kDmaWN / 2));
-    const int wm0 = kpair ? 0 : khalf * WTM, wn0 = (npair ? (qw & 1) : qw) * WTN;
-    const bool split2 = kpair || npair;               // a K-split pair of waves per output block
-    const int kh = kpair ? khalf : (npair ? qw >> 1 : 0);   // this wave's K half
+    const int wm0 = kpair ? 0 : khalf * WTM, wn0 = qw * WTN;
+    const int kh = kpair ? khalf : 0;   // this wave's K half
     static_assert(kDmaWM == 2, "the N-quarter swizzle pairs two M halves");
     const int r32 = lane & 31, h = lane >> 5;
 
@@ -223,15 +219,9 @@ __global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(GemmBatch bat
     // same barrier sequence (one after the first chunk's loads, one per chunk)
     // as the loop below, without fragment reads, MFMAs or stores.  Kept apart
     // from that loop: a test inside it slowed the full tiles by 2-4%.
-    // B rows of an npair tile stop at its 128 columns (the rest read nothing).
-    auto b_operand = [&]() {
-        Operand o = P.B;
-        if (npair) o.rows = min(o.rows, n0 + BN / 2);
-        return o;
-    };
     if (m0 + wm0 >= P.M || n0 + wn0 >= P.N) {
         if (kc0 < kc1) {
-            const Operand opA = P.A, opB = b_operand();
+            const Operand opA = P.A, opB = P.B;
             dma_tile<AK, NW>(opA, m0, kc0, lds0, wave, lane);
             dma_tile<BKM, NW>(opB, n0, kc0, lds0 + TILE, wave, lane);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -246,7 +236,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(GemmBatch bat
                 __syncthreads();
             }
         }
-        if (split2) __syncthreads();   // the hand-over of the second half's sums
+        if (kpair) __syncthreads();   // the hand-over of the second half's sums
         return;
     }
 
@@ -262,7 +252,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(GemmBatch bat
     // tiles of one column block share them out: tile row tm sums its own
     // contiguous share of the K chunks, so that no tile row carries all of
     // that work (a launch ends with its slowest tile).
-    const bool do_bsum = HAS_BSUM && (P.bsum != nullptr) && wm0 == 0 && !split2;
+    const bool do_bsum = HAS_BSUM && (P.bsum != nullptr) && wm0 == 0 && !kpair;
     float bs[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) bs[j] = 0.f;
@@ -272,7 +262,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(GemmBatch bat
         const FragAddr<BKM, TN> fb(wn0, lane);
         // Local copies of the operand descriptions: read once from the kernel
         // arguments instead of once per chunk.
-        const Operand opA = P.A, opB = b_operand();
+        const Operand opA = P.A, opB = P.B;
         dma_tile<AK, NW>(opA, m0, kc0, lds0, wave, lane);
         dma_tile<BKM, NW>(opB, n0, kc0, lds0 + TILE, wave, lane);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -351,7 +341,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(GemmBatch bat
         };
         using Four = std::integral_constant<int, 4>;
         using Two = std::integral_constant<int, 2>;
-        if (split2)
+        if (kpair)
             run(std::false_type{}, Two{});
         else if constexpr (HAS_BSUM) {
             if (do_bsum) {
@@ -368,13 +358,12 @@ __global__ __launch_bounds__(kDmaThreads, 1) void gemm_bf16_kernel(GemmBatch bat
         }
     }
 
-    if (split2) {
+    if (kpair) {
         // Hand-over: the waves of the second K half store their sums in the
-        // (now idle) operand stages, 32 KB per output block (kpair: per N
-        // quarter; npair: per M half and N quarter), lane-interleaved 16-byte
-        // vectors; the first K half adds them.  The last chunk's barrier has
-        // retired every fragment read of the stages.
-        const int reg = kpair ? wn0 / WTN : 2 * khalf + (qw & 1);
+        // (now idle) operand stages, 32 KB per N quarter, lane-interleaved
+        // 16-byte vectors; the first K half adds them.  The last chunk's
+        // barrier has retired every fragment read of the stages.
+        const int reg = qw;
         char* hand = (reg < 2 ? lds0 : lds1) + (reg & 1) * (STAGE / 2);
         static_assert(TM * TN * 16 * 4 * 64 == STAGE / 2, "one wave's sums fill half a stage");
         if (kh == 1) {
