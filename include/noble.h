@@ -143,7 +143,10 @@ noble_status noble_linear_workspace_size(const noble_linear_desc* desc,
 /* Scratch bytes the forward alone needs (at most the scratch_bytes of
  * noble_linear_workspace_size, which covers both calls): a forward-only or
  * inference caller may pass a buffer of this size to noble_linear_fwd.
- * Same errors as noble_linear_workspace_size; makes no HIP call. */
+ * Same errors as noble_linear_workspace_size; makes no HIP call.  A layer of
+ * few tokens runs faster with this much; the forward accepts any buffer that
+ * holds the bf16 branch output [T, R] and the float32 partials of x W_down
+ * that the unsplit form uses. */
 noble_status noble_linear_fwd_scratch_size(const noble_linear_desc* desc,
                                            size_t* scratch_bytes);
 

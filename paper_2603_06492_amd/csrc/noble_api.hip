@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "noble.h"
+#include "noble_finish.hpp"
 #include "noble_gemm_dma.hpp"
 #include "noble_gemm_tile.hpp"
 #include "noble_init.hpp"
@@ -29,6 +30,7 @@ constexpr int64_t kMaxDim = int64_t(1) << 20;
 constexpr int kMaxGroups = 4;
 constexpr int64_t kMaxTokens = (int64_t(1) << 31) - 4096;
 constexpr size_t kAlign = 256;
+constexpr size_t kStaticScratchBytes = NOBLE_STATIC_SCRATCH_BYTES;   // scratch of noble_linear_fwd_static
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -152,13 +154,22 @@ size_t copies_need(const noble_linear_desc* d) {
     return align_up((size_t)nvec(d) * kChainCopies * rank_total(d) * 4);
 }
 size_t wgrad_need(const noble_linear_desc* d);
-size_t fwd_scratch_need(const noble_linear_desc* d) {
+// The least scratch a forward runs with (its parts above).
+size_t fwd_scratch_min(const noble_linear_desc* d) {
     return d->r > 0 ? scratch_region(d) + partial_need(d) : 0;
 }
-size_t scratch_need(const noble_linear_desc* d) {
-    return (d->r > 0 ? fwd_scratch_need(d) + bwd_regions(d) * scratch_region_w(d) + copies_need(d) : 0) +
+// The least scratch a backward runs with.
+size_t bwd_scratch_need(const noble_linear_desc* d) {
+    return (d->r > 0 ? fwd_scratch_min(d) + bwd_regions(d) * scratch_region_w(d) + copies_need(d) : 0) +
            wgrad_need(d);
 }
+// A forward whose x W is split over K (plan_fwd) uses the forward's part of
+// the scratch differently: C2, then the float32 partials of x W_down
+// [S][T][R] and of x W [S][T][d_out].  The size queries count the larger of
+// the two layouts; a call with less scratch runs unsplit.
+size_t fwd_split_need(const noble_linear_desc* d);
+size_t fwd_scratch_need(const noble_linear_desc* d) { return std::max(fwd_scratch_min(d), fwd_split_need(d)); }
+size_t scratch_need(const noble_linear_desc* d) { return std::max(bwd_scratch_need(d), fwd_split_need(d)); }
 size_t reserve_need(const noble_linear_desc* d) { return (size_t)d->T * rank_total(d) * 4; }
 
 // A required buffer: non-NULL and 16-byte aligned, unless it holds no bytes.
@@ -210,7 +221,6 @@ int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // passes this name to a kernel (in host code it is only a stand-in for the
 // device symbol): each device's address comes from hipGetSymbolAddress,
 // taken once per device with that device current, and cached here.
-constexpr size_t kStaticScratchBytes = NOBLE_STATIC_SCRATCH_BYTES;
 static __device__ __align__(256) char g_static_scratch[kStaticScratchBytes];
 std::atomic<void*> g_static_scratch_addr[256];
 
@@ -312,6 +322,10 @@ double tile_time(const TileCost& t, int64_t blocks, int nk) {
     const double f = nk * t.c_full + t.e_full, p = nk * t.c_part + t.e_part;
     return (double)full * f + (rem == 0 ? 0.0 : (rem * 10 <= t.slots * 6 ? p : f));
 }
+double tile_cost(TileId i, int64_t G, int64_t M, int64_t N, int nk) {
+    const TileCost& t = kTileCost[i];
+    return tile_time(t, G * ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), nk);
+}
 // The tile of G problems [M, N] with nk K chunks (see kTileCost).
 TileId pick_tile(int64_t G, int64_t M, int64_t N, int nk) {
     TileId best = kTile256;
@@ -327,6 +341,67 @@ TileId pick_tile(int64_t G, int64_t M, int64_t N, int nk) {
         }
     }
     return best;
+}
+
+// Split forward (bf16, r > 0): x W and x W_down as K pieces of one launch,
+// then the chain, then y_finish_kernel.  split = 0: the rank projection, the
+// chain and the K-extended product instead.
+//
+// A layer of few output tiles reads W through a few CUs: one token of
+// 2048 -> 3 x 2048 ran 48 workgroups of 34 K chunks in 20 us of the call's
+// 37.8.  Splitting K costs the partials' traffic and one more pass, so the
+// rule compares both forms by cost: the rank projection (fixed + per chunk)
+// and the tile model of the K-extended product, against the tile model of the
+// pieces (at least the time W takes from HBM), the partials at 5.9 MB per us
+// and the finishing launch.  The chain is in both.  At most 4 pieces: the
+// chain and the finish read four partials in one round trip, and 6 or 8
+// measured slower everywhere.  Measured over 41 shapes of 1 to 2048 tokens
+// (cold weights, us, unsplit / split): 1 x 2048 -> 6144 37.8 / 22.7,
+// 16 x 2048 -> 8192 37.8 / 24.8, 777 x 8192 -> 2048 94 / 60, 1600 x 4096 ->
+// 768 64 / 40, 2048 x 4096 -> 1024 55 / 44; at the line 700 x 1024 -> 3072
+// 31.4 / 32.7 and 1100 x 512 -> 1536 29.2 / 31.5 (unsplit taken).  The rule's
+// choice is on average 1% off the best of the 13 forms measured.
+// The layout never exceeds the static scratch, so that noble_linear_fwd_static
+// and noble_linear_fwd take the same form.
+struct FwdPlan {
+    TileId tile;
+    int split;
+};
+size_t split_need(const noble_linear_desc* d, int S) {
+    return scratch_region(d) + align_up((size_t)S * d->T * rank_total(d) * 4) +
+           align_up((size_t)S * d->T * d->d_out * 4);
+}
+FwdPlan plan_fwd(const noble_linear_desc* d) {
+    FwdPlan w{kTile256, 0};
+    if (d->dtype != NOBLE_BF16 || d->r == 0 || d->T == 0) return w;
+    const int64_t T = d->T, R = rank_total(d), dog = group_dout(d);
+    const int G = ngroups(d), nk1 = cdiv(d->d_in, 64), J = proj_jobs(d);
+    constexpr double kProjFixed = 5.3, kProjChunk = 0.24, kFinFixed = 5.4, kPartBytesPerUs = 5.9e6, kHbmBytesPerUs = 4.3e6;
+    const int Sp = proj_split(T, d->d_in, J);
+    const int64_t pwaves = ((T + kPjRows - 1) / kPjRows * Sp * J + 255) / 256;
+    const int nk = nk1 + cdiv(d->r, 64);
+    double best = kProjFixed + kProjChunk * cdiv(nk1, Sp) * (double)pwaves +
+                  tile_cost(pick_tile(G, T, dog, nk), G, T, dog, nk);
+    const double hbm = (double)d->d_in * (double)(d->d_out + R) * 2 / kHbmBytesPerUs + 3.0;
+    for (int i = kTile256x128; i < kTileIds; ++i) {
+        const TileCost& t = kTileCost[i];
+        const int64_t tiles = (T + t.bm - 1) / t.bm * ((d->d_out + t.bn - 1) / t.bn + (R + t.bn - 1) / t.bn);
+        for (int s = 1; s <= 4 && 2 * s <= nk1; ++s) {
+            if (split_need(d, s) > kStaticScratchBytes || tiles * s >= (1 << 22)) break;
+            const double c = std::max(tile_time(t, tiles * s, cdiv(nk1, s)), hbm) +
+                             2.0 * s * (double)T * (double)(d->d_out + R) * 4 / kPartBytesPerUs + kFinFixed;
+            if (c < best) {
+                best = c;
+                w.tile = (TileId)i;
+                w.split = s;
+            }
+        }
+    }
+    return w;
+}
+size_t fwd_split_need(const noble_linear_desc* d) {
+    const FwdPlan w = plan_fwd(d);
+    return w.split > 0 ? split_need(d, w.split) : 0;
 }
 
 template <typename List>
@@ -594,6 +669,29 @@ noble_status launch_dense(const Batch<DenseBatch>& bt, TileId tile, hipStream_t 
     }
 }
 
+// The last launch of a split forward (noble_finish.hpp).
+noble_status launch_finish(const noble_linear_desc* d, const float* P, int S, const void* C2s, const void* Wu,
+                           const float* b, void* y, hipStream_t st) {
+    FinishArgs a{};
+    a.P = P;
+    a.pstride = d->T * d->d_out;
+    a.C2s = static_cast<const uint16_t*>(C2s);
+    a.Wu = static_cast<const uint16_t*>(Wu);
+    a.b = b;
+    a.y = static_cast<uint16_t*>(y);
+    a.T = (int)d->T;
+    a.S = S;
+    a.G = ngroups(d);
+    a.r = (int)d->r;
+    a.R = (int)rank_total(d);
+    a.dog = (int)group_dout(d);
+    a.dout = (int)d->d_out;
+    const dim3 grid((unsigned)((int64_t)cdiv(a.T, kFinRows) * a.G * cdiv(a.dog, kFinCols))), block(256);
+    if (a.r <= 64) return launch(y_finish_kernel<1>, grid, block, st, a);
+    if (a.r <= 128) return launch(y_finish_kernel<2>, grid, block, st, a);
+    return launch(y_finish_kernel<4>, grid, block, st, a);
+}
+
 // Empty batch for y or dx, G problems [M, N] of nk chunks each.
 template <typename E>
 Batch<DenseBatch> dense_batch(int64_t G, int64_t M, int64_t N, int nk, TileId& tile) {
@@ -766,7 +864,7 @@ void set_mixing(ChainArgs& a, const noble_linear_desc* d, const void* M, const f
 template <typename E>
 noble_status fwd_impl(const noble_linear_desc* d, const void* x, const void* W, const float* b, const void* Wd,
                       const float* w1, const float* p1, const void* M, const float* w2, const float* p2,
-                      const void* Wu, void* y, void* reserve, void* scratch, hipStream_t st) {
+                      const void* Wu, void* y, void* reserve, void* scratch, size_t scratch_bytes, hipStream_t st) {
     constexpr int BK = Elt<E>::BK;
     constexpr size_t ES = sizeof(E);
     const int64_t T = d->T, din = d->d_in, dout = d->d_out, r = d->r;
@@ -786,6 +884,23 @@ noble_status fwd_impl(const noble_linear_desc* d, const void* x, const void* W, 
         a.nk = cdiv(din, BK);
         if constexpr (sizeof(E) == 2) {
             float* P = reinterpret_cast<float*>(static_cast<char*>(scratch) + scratch_region(d));
+            const FwdPlan fp = plan_fwd(d);
+            if (fp.split > 0 && scratch_bytes >= split_need(d, fp.split)) {
+                const int nk = cdiv(din, BK);
+                float* Py = reinterpret_cast<float*>(reinterpret_cast<char*>(P) +
+                                                     align_up((size_t)fp.split * T * R * 4));
+                Batch<DenseBatch> bt;
+                bt.bm = kTileCost[fp.tile].bm;
+                bt.bn = kTileCost[fp.tile].bn;
+                const Operand X = operand1(seg(x, din, din), T);
+                bt.add(X, operand1(seg(W, dout, din), dout), (int)T, (int)dout, nk, nullptr, dout, true, nullptr,
+                       nullptr, fp.split, Py);
+                bt.add(X, operand1(seg(Wd, R, din), R), (int)T, (int)R, nk, nullptr, R, true, nullptr, nullptr,
+                       fp.split, P);
+                NOBLE_TRY((launch_dense<E, false>(bt, fp.tile, st)));
+                NOBLE_TRY(launch_branch(true, d, a, P, fp.split, st));
+                return launch_finish(d, Py, fp.split, C2s, Wu, b, y, st);
+            }
             const int S = proj_split(T, din, proj_jobs(d));
             NOBLE_TRY(launch_proj(true, d, x, Wd, P, S, st));
             NOBLE_TRY(launch_branch(true, d, a, P, S, st));
@@ -832,7 +947,7 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
     const size_t regw = scratch_region_w(d);
     char* base = static_cast<char*>(scratch);
     char* C2s = base;
-    char* C1s = base + fwd_scratch_need(d);
+    char* C1s = base + fwd_scratch_min(d);
     char* dH2s = C1s + regw;
     char* dHs = dH2s + regw;
     char* C2ms = three ? dHs + regw : nullptr;   // 3-layer form: the middle C2 and dH3
@@ -1102,8 +1217,8 @@ noble_status fwd_check(const noble_linear_desc* desc, const void* x, const void*
         NOBLE_TRY(optional(reserve));   // NULL: inference-only forward
         if (scratch_bytes >= 0) {
             NOBLE_TRY(need(scratch, rows));
-            if ((size_t)scratch_bytes < fwd_scratch_need(desc)) return NOBLE_ERR_WORKSPACE_TOO_SMALL;
-        } else if (fwd_scratch_need(desc) > kStaticScratchBytes) {
+            if ((size_t)scratch_bytes < fwd_scratch_min(desc)) return NOBLE_ERR_WORKSPACE_TOO_SMALL;
+        } else if (fwd_scratch_min(desc) > kStaticScratchBytes) {
             return NOBLE_ERR_WORKSPACE_TOO_SMALL;
         }
     }
@@ -1124,8 +1239,10 @@ noble_status noble_linear_fwd(const noble_linear_desc* desc, const void* x, cons
     NOBLE_TRY(check_device());
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (desc->dtype == NOBLE_BF16)
-        return fwd_impl<uint16_t>(desc, x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, reserve, scratch, st);
-    return fwd_impl<float>(desc, x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, reserve, scratch, st);
+        return fwd_impl<uint16_t>(desc, x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, reserve, scratch,
+                                  scratch_bytes, st);
+    return fwd_impl<float>(desc, x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, reserve, scratch,
+                                  scratch_bytes, st);
 }
 
 noble_status noble_linear_fwd_static(const noble_linear_desc* desc, const void* x, const void* W, const float* b,
@@ -1140,8 +1257,10 @@ noble_status noble_linear_fwd_static(const noble_linear_desc* desc, const void* 
     if (desc->r > 0) NOBLE_TRY(static_scratch(dev, &scratch));
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (desc->dtype == NOBLE_BF16)
-        return fwd_impl<uint16_t>(desc, x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, reserve, scratch, st);
-    return fwd_impl<float>(desc, x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, reserve, scratch, st);
+        return fwd_impl<uint16_t>(desc, x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, reserve, scratch,
+                                  kStaticScratchBytes, st);
+    return fwd_impl<float>(desc, x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, reserve, scratch,
+                                  kStaticScratchBytes, st);
 }
 
 noble_status noble_linear_bwd(const noble_linear_desc* desc, const void* dy, const void* x, const void* W,
@@ -1177,9 +1296,9 @@ noble_status noble_linear_bwd(const noble_linear_desc* desc, const void* dy, con
         NOBLE_TRY(l2 ? need(domega2, true) : optional(domega2));
         NOBLE_TRY(l2 ? need(dphi2, true) : optional(dphi2));
     }
-    if (scratch_need(desc) > 0) {
+    if (bwd_scratch_need(desc) > 0) {
         NOBLE_TRY(need(scratch, rows));
-        if (rows && scratch_bytes < scratch_need(desc)) return NOBLE_ERR_WORKSPACE_TOO_SMALL;
+        if (rows && scratch_bytes < bwd_scratch_need(desc)) return NOBLE_ERR_WORKSPACE_TOO_SMALL;
     }
     NOBLE_TRY(check_device());
     hipStream_t st = static_cast<hipStream_t>(stream);
