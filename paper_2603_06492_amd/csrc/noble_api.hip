@@ -273,9 +273,9 @@ Operand operand2(Seg s0, Seg s1, int nk1, int64_t rows) {
     return o;
 }
 
-// Square output tile of the large products: 256 on the bf16 path; 128 on
-// the float32 path, which serves small layers (a 256 tile of a 64 x 64
-// output would leave one wave doing 16 times the needed work on one CU).
+// Square output tile of the large products, as the weight-gradient plan and
+// the size limits count it: 256 on the bf16 path; 128 on the float32 path,
+// whose launches run it or 64 (f32_tile).
 template <typename E>
 constexpr int gemm_tile() {
     return sizeof(E) == 2 ? 256 : 128;
@@ -402,6 +402,19 @@ FwdPlan plan_fwd(const noble_linear_desc* d) {
 size_t fwd_split_need(const noble_linear_desc* d) {
     const FwdPlan w = plan_fwd(d);
     return w.split > 0 ? split_need(d, w.split) : 0;
+}
+
+// Output tile of a float32 launch that has b128 workgroups of 128 x 128 tiles
+// or b64 of 64 x 64.  The float32 MFMAs are slow enough (a 128 x 128 tile's
+// 32-element chunk takes 1.7 us) that a launch of less than a wave of 128 x
+// 128 tiles is bound by its longest CU; a 64 x 64 tile takes 0.28 of the time
+// of a 128 x 128 one when both fill the chip, and several share a CU.
+// Forward / backward, 128 against 64 (us): 2048 x 768 -> 768 83 / 130 and
+// 60 / 101, 256 x 64 -> 64 16 / 42 and 11 / 24, 4096 x 256 -> 256 34 / 67 and
+// 22 / 47; at a full wave, 4096 x 1024 -> 1024, 116 / 233 and 117 / 234, and
+// beyond, 8192 x 2048 -> 2048, 638 / 1333 and 711 / 1415.
+int f32_tile(int64_t b128, int64_t b64) {
+    return 0.28 * (double)((b64 + 255) / 256) < (double)((b128 + 255) / 256) ? 64 : 128;
 }
 
 template <typename List>
@@ -637,9 +650,11 @@ template <typename E>
 noble_status launch_wgrad(const Batch<GemmBatch>& bt, hipStream_t st) {
     if constexpr (sizeof(E) == 2)
         return launch(gemm_bf16_kernel<false, false, true, 0, GemmBatch>, dim3(bt.blocks), dim3(kDmaThreads), st, bt.b);
+    else if (bt.bm == 64)
+        return launch(gemm_kernel<E, 64, 64, false, false, true, GemmBatch>, dim3(bt.blocks), dim3(kThreads), st, bt.b);
     else
-        return launch(gemm_kernel<E, gemm_tile<E>(), gemm_tile<E>(), false, false, true, GemmBatch>, dim3(bt.blocks),
-                      dim3(kThreads), st, bt.b);
+        return launch(gemm_kernel<E, 128, 128, false, false, true, GemmBatch>, dim3(bt.blocks), dim3(kThreads), st,
+                      bt.b);
 }
 
 // y (BKM = false) or dx (BKM = true) on the tile that its batch was built
@@ -663,9 +678,10 @@ noble_status launch_dense(const Batch<DenseBatch>& bt, TileId tile, hipStream_t 
         if (!BKM && plain)
             return launch(gemm_bf16_kernel<true, BKM, false, 1, B>, grid, dim3(kDmaThreads), st, bt.b);
         return launch(gemm_bf16_kernel<true, BKM, false, 0, B>, grid, dim3(kDmaThreads), st, bt.b);
+    } else if (bt.bm == 64) {
+        return launch(gemm_kernel<E, 64, 64, true, BKM, false, B>, dim3(bt.blocks), dim3(kThreads), st, bt.b);
     } else {
-        return launch(gemm_kernel<E, gemm_tile<E>(), gemm_tile<E>(), true, BKM, false, B>, dim3(bt.blocks),
-                      dim3(kThreads), st, bt.b);
+        return launch(gemm_kernel<E, 128, 128, true, BKM, false, B>, dim3(bt.blocks), dim3(kThreads), st, bt.b);
     }
 }
 
@@ -697,9 +713,14 @@ template <typename E>
 Batch<DenseBatch> dense_batch(int64_t G, int64_t M, int64_t N, int nk, TileId& tile) {
     Batch<DenseBatch> bt;
     tile = kTile256;
-    if (sizeof(E) == 2) tile = pick_tile(G, M, N, nk);
-    bt.bm = sizeof(E) == 2 ? kTileCost[tile].bm : gemm_tile<E>();
-    bt.bn = sizeof(E) == 2 ? kTileCost[tile].bn : gemm_tile<E>();
+    if constexpr (sizeof(E) == 2) {
+        tile = pick_tile(G, M, N, nk);
+        bt.bm = kTileCost[tile].bm;
+        bt.bn = kTileCost[tile].bn;
+    } else {
+        auto blocks = [&](int64_t t) { return G * ((M + t - 1) / t) * ((N + t - 1) / t); };
+        bt.bm = bt.bn = f32_tile(blocks(128), blocks(64));
+    }
     return bt;
 }
 
@@ -1076,6 +1097,14 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
         };
         Batch<GemmBatch> bt;
         bt.bm = bt.bn = gemm_tile<E>();
+        if constexpr (sizeof(E) == 4) {
+            auto blocks = [&](int64_t t) {
+                auto tiles = [t](int64_t m, int64_t n) { return ((m + t - 1) / t) * ((n + t - 1) / t); };
+                return tiles(din, dout) * wp.split +
+                       (r > 0 ? (tiles(din, R) + G * (tiles(r, dog) + (two ? nm * tiles(r, r) : 0))) * wp.rank : 0);
+            };
+            bt.bm = bt.bn = f32_tile(blocks(128), blocks(64));
+        }
         const Operand xT = operand1(seg(x, din, T), din);
         const Operand dyN = operand1(seg(dy, dout, T), dout);
         bt.add(xT, dyN, (int)din, (int)dout, nkT, dW, dout, true, nullptr, db, wp.split,

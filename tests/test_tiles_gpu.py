@@ -39,3 +39,28 @@ def test_dense_products_on_every_tile(case):
     for k, e in rep.items():
         assert e <= TOL["bf16"], (k, e)
     assert dp.guards_intact(), "write outside an output buffer"
+
+
+F32_CASES = [
+    # id, T, d_in, d_out, r, groups: 64 x 64 tiles below a wave of 128 x 128 ones, 128 x 128 from a full wave on
+    ("f32_64_T63", 63, 40, 72, 8, 1),
+    ("f32_64_T65_g3", 65, 104, 3 * 136, 24, 3),
+    ("f32_64_T1030", 1030, 200, 328, 32, 1),
+    ("f32_128_T4100", 4100, 1032, 968, 16, 1),
+]
+
+
+@pytest.mark.parametrize("case", F32_CASES, ids=[c[0] for c in F32_CASES])
+def test_float32_products_on_both_tiles(case):
+    from paper_2603_06492_amd.runner import DeviceProblem
+    name, T, di, do, r, G = case
+    print(f"[tiles] {name}: T={T} d_in={di} d_out={do} r={r} groups={G}", flush=True)
+    p = inp.draw_projection(name, T, di, do, r, "f32", seed=78, bias_std=0.5, groups=G)
+    dp = DeviceProblem(p, canary=True)
+    dp.fwd()
+    dp.bwd()
+    rep = parity_report(dp.outputs(), oracle_outputs(p))
+    print(rep, flush=True)
+    for k, e in rep.items():
+        assert e <= TOL["f32"], (k, e)
+    assert dp.guards_intact(), "write outside an output buffer"
