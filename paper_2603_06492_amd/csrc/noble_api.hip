@@ -355,7 +355,8 @@ TileId pick_tile(int64_t G, int64_t M, int64_t N, int nk) {
 // pieces (at least the time W takes from HBM), the partials at 5.9 MB per us
 // and the finishing launch.  The chain is in both.  At most 4 pieces: the
 // chain and the finish read four partials in one round trip, and 6 or 8
-// measured slower everywhere.  Measured over 41 shapes of 1 to 2048 tokens
+// measured slower everywhere; at least four K chunks per piece, as in the rank
+// projection (shorter pieces gained 2% at most).  Measured over 41 shapes of 1 to 2048 tokens
 // (cold weights, us, unsplit / split): 1 x 2048 -> 6144 37.8 / 22.7,
 // 16 x 2048 -> 8192 37.8 / 24.8, 777 x 8192 -> 2048 94 / 60, 1600 x 4096 ->
 // 768 64 / 40, 2048 x 4096 -> 1024 55 / 44; at the line 700 x 1024 -> 3072
@@ -809,15 +810,17 @@ noble_status launch_branch(bool fwd, const noble_linear_desc* d, const ChainArgs
     a.r = (int)d->r;
     a.G = ngroups(d);
     a.R = (int)rank_total(d);
-    const int NT = rank_blocks(d);
-    const dim3 grid = flat_grid((int64_t)cdiv(d->T, kSkRows) * a.G), block(kThreads * NT);
     return with_act(d->activation, [&]<Act F, int L>() -> noble_status {
-        if (NT == 1)
-            return fwd ? launch(branch_fwd_kernel<F, L, 1>, grid, block, st, a)
-                       : launch(branch_bwd_kernel<F, L, 1>, grid, block, st, a);
-        if constexpr (L != 3)   // the 3-layer form is validated to r <= 128 (NT = 1)
-            return fwd ? launch(branch_fwd_kernel<F, L, 2>, grid, block, st, a)
-                       : launch(branch_bwd_kernel<F, L, 2>, grid, block, st, a);
+        auto run = [&]<int NW>() -> noble_status {
+            using Sh = SkShape<NW>;
+            const dim3 grid = flat_grid((int64_t)cdiv(d->T, kSkRows * Sh::TB) * a.G), block(64 * Sh::WAVES);
+            return fwd ? launch(branch_fwd_kernel<F, L, NW>, grid, block, st, a)
+                       : launch(branch_bwd_kernel<F, L, NW>, grid, block, st, a);
+        };
+        if (d->r <= 32) return run.template operator()<1>();
+        if (d->r <= 64) return run.template operator()<2>();
+        if (d->r <= 128) return run.template operator()<4>();
+        if constexpr (L != 3) return run.template operator()<8>();   // the 3-layer form is validated to r <= 128
         return NOBLE_ERR_BAD_SHAPE;
     });
 }

@@ -23,11 +23,13 @@
 //   one-application form C2 = f(H w1 + p1), which skips M and the second
 //   frequency/phase pair.
 //
-// The chain kernels run 32 tokens x one group's ranks per workgroup: four
-// waves (r <= 128) or eight (r <= 256), each owning 32 rank columns.  M [r, r]
-// is loaded into LDS once per workgroup as 128 x 128 tiles in its HBM
-// orientation [r_in][r_out]; C1 M reads it with ds_read_b64_tr_b16 and
-// dH2 M^T with ds_read_b128.
+// A chain wave owns 32 tokens x 32 rank columns of one group; NW = 1, 2, 4
+// or 8 waves (r <= 32 NW) cover a group's ranks.  A workgroup has four waves
+// (eight for NW = 8), so at r <= 32 or 64 it takes four or two blocks of 32
+// tokens: with one block, three or two of its waves would own columns past r.
+// M [r, r] is loaded into LDS once per workgroup as tiles of 128 columns in
+// its HBM orientation [r_in][r_out]; C1 M reads it with ds_read_b64_tr_b16
+// and dH2 M^T with ds_read_b128.
 //
 // Grouped layers (several output column blocks of one x, each with its own
 // branch, e.g. Q, K and V): the rank side is stored token-major as [T, G r];
@@ -42,18 +44,24 @@ namespace noble {
 
 constexpr int kSkRows = 32;     // tokens per chain workgroup
 constexpr int kSkN = 128;       // rank columns of one M tile
-constexpr int kSkM = kSkN * kSkN * 2;     // one M tile, 128 x 128 bf16
-constexpr int kSkC = kSkRows * kSkN * 2;  // 32 x 128 bf16 of the C1 / dH2 operand tile
-constexpr int kSkMaxNT = 2;               // ranks up to 2 x 128 per group
-// LDS of a chain workgroup with L - 1 mixing matrices of NT x NT M tiles
-// and two 32 x 128 NT operand tiles: the high and low bf16 parts of the
-// mixing operand (C1, C2, dH2 or dH3).  The 3-layer form runs at NT = 1.
-template <int NT, int L = 2>
-constexpr int sk_lds() {
-    return (L == 3 ? 2 : 1) * NT * NT * kSkM + 2 * NT * kSkC;
-}
-static_assert(sk_lds<kSkMaxNT>() <= 160 * 1024, "chain LDS exceeds a CU's 160 KB");
-static_assert(sk_lds<1, 3>() <= 160 * 1024, "chain LDS exceeds a CU's 160 KB");
+// Shape of a chain workgroup whose NW waves cover a group's ranks.
+template <int NW>
+struct SkShape {
+    static_assert(NW == 1 || NW == 2 || NW == 4 || NW == 8, "waves per 32 tokens");
+    static constexpr int WAVES = NW == 8 ? 8 : 4;
+    static constexpr int TB = WAVES / NW;             // 32-token blocks per workgroup
+    static constexpr int NT = NW == 8 ? 2 : 1;        // 128-column M tiles per side
+    static constexpr int MROWS = NW < 4 ? 32 * NW : kSkN;
+    static constexpr int MT = MROWS * kSkN * 2;       // one M tile, MROWS x 128 bf16
+    // one 32-token operand tile (the high or low bf16 part of C1, C2, dH2 or
+    // dH3), in 64-column chunks of 4 KB
+    static constexpr int CT = (NW < 2 ? 1 : NW / 2) * 4096;
+    static constexpr int KS = NW < 4 ? 2 * NW : 8;    // K steps of 16 ranks per M tile
+    // M (and M') and the two operand tiles of each token block
+    static constexpr int lds(int L) { return (L == 3 ? 2 : 1) * NT * NT * MT + 2 * TB * CT; }
+};
+static_assert(SkShape<8>::lds(2) <= 160 * 1024, "chain LDS exceeds a CU's 160 KB");
+static_assert(SkShape<4>::lds(3) <= 160 * 1024, "chain LDS exceeds a CU's 160 KB");
 
 // A float32 value as the sum of two bf16 values (round to nearest even
 // twice): hi carries the leading 8 significant bits, lo the next 8.  hi + lo
@@ -197,12 +205,13 @@ __device__ __forceinline__ void proj_dma(const Operand& A, const Operand& B, int
     }
 }
 
-// M [r, r] into LDS as NT x NT tiles of [128 r_in][256 B]; tile i NT + j
+// M [r, r] into LDS as NT x NT tiles of [MROWS r_in][256 B]; tile i NT + j
 // holds M[128 i .., 128 j ..], and 16-byte segment s of tile row p sits at
 // physical segment s ^ 4(p & 3).  Rows / columns past r read as zero.
-template <int NT>
+template <int NW>
 __device__ __forceinline__ void m_dma(const uint16_t* M, int r, char* dst, int wave, int lane) {
-    constexpr int NW = 4 * NT;   // waves of the workgroup
+    using S = SkShape<NW>;
+    constexpr int NT = S::NT;
     const i32x4 rs = make_desc(reinterpret_cast<const char*>(M), (int64_t)r * r * 2);
     const int kq = lane >> 4;
     const int seg = (lane & 15) ^ (4 * kq);
@@ -212,10 +221,10 @@ __device__ __forceinline__ void m_dma(const uint16_t* M, int r, char* dst, int w
         for (int tj = 0; tj < NT; ++tj) {
             const int col = 128 * tj + 8 * seg;
             const uint32_t vo = col < r ? (uint32_t)(((int64_t)(128 * ti + kq) * r + col) * 2) : kOOB;
-            char* tile = dst + (ti * NT + tj) * kSkM;
+            char* tile = dst + (ti * NT + tj) * S::MT;
 #pragma unroll
-            for (int i = 0; i < 32 / NW; ++i) {
-                const int b = NW * i + wave;   // tile rows 4b .. 4b+3
+            for (int i = 0; i < S::MROWS / 4 / S::WAVES; ++i) {
+                const int b = S::WAVES * i + wave;   // tile rows 4b .. 4b+3
                 dma16(rs, tile + b * 1024, vo, (uint32_t)((int64_t)4 * b * r * 2));
             }
         }
@@ -248,23 +257,24 @@ __device__ __forceinline__ int ctile_off(int row, int col) {
     return (col >> 6) * 4096 + row * 128 + ((((col >> 3) & 7) ^ ((row ^ (row >> 3)) & 7)) << 4) + (col & 7) * 2;
 }
 
-// acc (one 32x32 block per wave, columns 32 w .. of the 128 NT) over the K
-// steps of a [32 x 128 NT] operand held as two tiles in LDS (A, K-major: its
+// acc (one 32x32 block per wave, columns 32 w .., w < NW) over the K steps
+// of a [32 x 32 NW] operand held as two tiles in LDS (A, K-major: its
 // high bf16 part at `chi`, its low part at `clo`) times M (TRANS_M = false:
 // B(k, n) = M[k][n]) or M^T (B(k, n) = M[n][k]), M held as NT x NT tiles.
 // Each K step issues two MFMAs on the same M fragment, high part first.
-template <bool TRANS_M, int NT>
+template <bool TRANS_M, int NW>
 __device__ __forceinline__ void mix_mma(const char* chi, const char* clo, const char* mt, int wave, int lane,
                                         f32x16& acc) {
+    constexpr int NT = SkShape<NW>::NT;
     const int r32 = lane & 31, h = lane >> 5;
     const int wl = wave & 3, nb = wave >> 2;   // 32-column block within tile column nb
     const uint32_t tb = tr_base(wl, lane);
     const int p = 32 * wl + r32;   // tile row of M for the M^T product
 #pragma unroll
     for (int kb = 0; kb < NT; ++kb) {
-        const char* tile = mt + (TRANS_M ? nb * NT + kb : kb * NT + nb) * kSkM;
+        const char* tile = mt + (TRANS_M ? nb * NT + kb : kb * NT + nb) * SkShape<NW>::MT;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
+        for (int s = 0; s < SkShape<NW>::KS; ++s) {
             const int ql = 2 * s + h;     // 8-element K group of this lane within the tile
             const int q = 16 * kb + ql;   // ... within the whole rank
             const uint32_t ao = (uint32_t)((q >> 3) * 4096 + r32 * 128 + ((((q & 7) ^ (r32 & 7) ^ (r32 >> 3))) << 4));
@@ -283,17 +293,18 @@ __device__ __forceinline__ void mix_mma(const char* chi, const char* clo, const 
 
 // One more pass of the same product over a third operand tile `c` (the low
 // part of a three-part split), accumulated into acc.
-template <bool TRANS_M, int NT>
+template <bool TRANS_M, int NW>
 __device__ __forceinline__ void mix_mma1(const char* c, const char* mt, int wave, int lane, f32x16& acc) {
+    constexpr int NT = SkShape<NW>::NT;
     const int r32 = lane & 31, h = lane >> 5;
     const int wl = wave & 3, nb = wave >> 2;
     const uint32_t tb = tr_base(wl, lane);
     const int p = 32 * wl + r32;
 #pragma unroll
     for (int kb = 0; kb < NT; ++kb) {
-        const char* tile = mt + (TRANS_M ? nb * NT + kb : kb * NT + nb) * kSkM;
+        const char* tile = mt + (TRANS_M ? nb * NT + kb : kb * NT + nb) * SkShape<NW>::MT;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
+        for (int s = 0; s < SkShape<NW>::KS; ++s) {
             const int ql = 2 * s + h;
             const int q = 16 * kb + ql;
             const u32x4 av = *reinterpret_cast<const u32x4*>(c + (q >> 3) * 4096 + r32 * 128 +
@@ -453,21 +464,24 @@ __device__ __forceinline__ float block_colsum(const float (&x)[16]) {
     return s + __shfl_xor(s, 32);
 }
 
-// Workgroup b of a chain launch: token block b / G, group b % G.  Wave w
-// owns rank column 32 w + lane % 32 of the group (NT = 1: 4 waves, 128 ranks;
-// NT = 2: 8 waves, 256 ranks).
+// Workgroup b of a chain launch: TB blocks of 32 tokens from TB (b / G),
+// group b % G; `tb` is the wave's block.  Blocks past T have rows past T only:
+// their loads return zero and their stores are dropped.
 struct ChainPos {
     int row0, g, c0;
 };
-__device__ __forceinline__ ChainPos chain_pos(const BranchArgs& a) {
+template <int NW>
+__device__ __forceinline__ ChainPos chain_pos(const BranchArgs& a, int tb) {
     const int64_t wg = flat_block();
-    const int tb = (int)(wg / a.G);
-    const int g = (int)(wg - (int64_t)tb * a.G);
-    return ChainPos{tb * kSkRows, g, g * a.r};
+    const int b = (int)(wg / a.G);
+    const int g = (int)(wg - (int64_t)b * a.G);
+    return ChainPos{(b * SkShape<NW>::TB + tb) * kSkRows, g, g * a.r};
 }
 // False for the surplus workgroups of the last grid row.
+template <int NW>
 __device__ __forceinline__ bool chain_live(const BranchArgs& a) {
-    return flat_block() < (int64_t)((a.T + kSkRows - 1) / kSkRows) * a.G;
+    constexpr int rows = kSkRows * SkShape<NW>::TB;
+    return flat_block() < (int64_t)((a.T + rows - 1) / rows) * a.G;
 }
 
 // Buffer resource over a token-major array with row stride `ld` elements
@@ -477,6 +491,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base, in
                                                             int64_t c0, int es) {
     return make_rsrc(reinterpret_cast<const char*>(base) + ((int64_t)row0 * ld + c0) * es,
                      (int64_t)(T - row0) * ld * es);
+}
+// Element `col` of the group's part of an [R] vector (zero past r).
+__device__ __forceinline__ float rank_vec(const BranchArgs& a, const float* v, const ChainPos& q, int col) {
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(reinterpret_cast<const char*>(v + q.c0), (int64_t)a.r * 4);
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (uint32_t)col * 4, 0, 0));
 }
 // The group's columns of a [T, R] array.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t group_rsrc(const void* base, const BranchArgs& a, const ChainPos& q,
@@ -489,7 +508,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t group_rsrc(const void* base, c
 // 8(v/4) + 4h + v%4, column col): P goes to the operand tiles in three bf16
 // parts (two passes), so the product is as accurate as a float32 one.
 // Leaves the tiles free (a barrier after the last read).
-template <bool TRANS, int NT>
+template <bool TRANS, int NW>
 __device__ __forceinline__ void mix3(const float (&pv)[16], char* chi, char* clo, const char* mt, int wave, int lane,
                                      int col, f32x16& acc) {
     const int h = lane >> 5;
@@ -504,13 +523,13 @@ __device__ __forceinline__ void mix3(const float (&pv)[16], char* chi, char* clo
         acc[v] = 0.f;
     }
     __syncthreads();
-    mix_mma<TRANS, NT>(chi, clo, mt, wave, lane, acc);
+    mix_mma<TRANS, NW>(chi, clo, mt, wave, lane, acc);
     __syncthreads();   // every wave is done with the high part
 #pragma unroll
     for (int v = 0; v < 16; ++v)
         *reinterpret_cast<uint16_t*>(chi + ctile_off(8 * (v >> 2) + 4 * h + (v & 3), col)) = lo[v];
     __syncthreads();
-    mix_mma1<TRANS, NT>(chi, mt, wave, lane, acc);
+    mix_mma1<TRANS, NW>(chi, mt, wave, lane, acc);
     __syncthreads();   // done reading the tiles
 }
 
@@ -522,30 +541,35 @@ __device__ __forceinline__ void mix3(const float (&pv)[16], char* chi, char* clo
 // then the low part from the first tile again), so every mixing product is
 // as accurate as a float32 one and the cosine arguments carry float32
 // rounding only.
-template <Act F, int L, int NT>
-__global__ __launch_bounds__(kThreads * NT, 1) void branch_fwd_kernel(BranchArgs a) {
-    static_assert(L != 3 || NT == 1, "the 3-layer form holds both mixing matrices in LDS at r <= 128");
-    __shared__ __attribute__((aligned(1024))) char lds[sk_lds<NT, L>()];
+template <Act F, int L, int NW>
+__global__ __launch_bounds__(64 * SkShape<NW>::WAVES, 1) void branch_fwd_kernel(BranchArgs a) {
+    static_assert(L != 3 || NW <= 4, "the 3-layer form holds both mixing matrices in LDS at r <= 128");
+    using S = SkShape<NW>;
+    __shared__ __attribute__((aligned(1024))) char lds[S::lds(L)];
     char* mt = lds;
-    char* mt2 = mt + NT * NT * kSkM;   // 3-layer form
-    char* chi = mt + (L == 3 ? 2 : 1) * NT * NT * kSkM;
-    char* clo = chi + NT * kSkC;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    char* mt2 = mt + S::NT * S::NT * S::MT;   // 3-layer form
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, h = lane >> 5;
-    if (!chain_live(a)) return;
-    const ChainPos q = chain_pos(a);
+    if (!chain_live<NW>(a)) return;
+    const int tb = wid / NW, wave = wid % NW;   // token block of the workgroup, 32 rank columns
+    const ChainPos q = chain_pos<NW>(a, tb);
+    char* chi = mt + (L == 3 ? 2 : 1) * S::NT * S::NT * S::MT + 2 * tb * S::CT;
+    char* clo = chi + S::CT;
     const int r = a.r, R = a.R;
 
     // M (and M') land while the partials are summed
-    if constexpr (L >= 2) m_dma<NT>(a.M + (int64_t)q.g * r * r, r, mt, wave, lane);
-    if constexpr (L == 3) m_dma<NT>(a.M2 + (int64_t)q.g * r * r, r, mt2, wave, lane);
+    if constexpr (L >= 2) m_dma<NW>(a.M + (int64_t)q.g * r * r, r, mt, wid, lane);
+    if constexpr (L == 3) m_dma<NW>(a.M2 + (int64_t)q.g * r * r, r, mt2, wid, lane);
     // acc[v]: token row0 + 8(v/4) + 4h + v%4, rank column 32 wave + r32 of the group
     const int col = 32 * wave + r32;
+    const bool cv = col < r;
+    // the frequencies and phases arrive with the partials, in one round trip
+    const float w1 = rank_vec(a, a.w1, q, col), p1 = rank_vec(a, a.p1, q, col);
+    const float w2 = L >= 2 ? rank_vec(a, a.w2, q, col) : 0.f, p2 = L >= 2 ? rank_vec(a, a.p2, q, col) : 0.f;
+    const float w3 = L == 3 ? rank_vec(a, a.w3, q, col) : 0.f, p3 = L == 3 ? rank_vec(a, a.p3, q, col) : 0.f;
     f32x16 acc;
     sum_partials(a, q.row0, q.c0, col, h, acc);
 
-    const bool cv = col < r;
-    const float w1 = cv ? a.w1[q.c0 + col] : 0.f, p1 = cv ? a.p1[q.c0 + col] : 0.f;
     const __amdgpu_buffer_rsrc_t rh = group_rsrc(a.H, a, q, 4);
     const __amdgpu_buffer_rsrc_t rc = group_rsrc(a.C2s, a, q, 2);
     const uint32_t vo4 = cv ? (uint32_t)(((4 * h) * R + col) * 4) : kOOB;
@@ -573,18 +597,16 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_fwd_kernel(BranchArgs
             __builtin_amdgcn_raw_buffer_store_b16((uint16_t)f2bf(c1[v]), rc, vo2, soff(v, 2), 0);
         return;
     }
-    const float w2 = cv ? a.w2[q.c0 + col] : 0.f, p2 = cv ? a.p2[q.c0 + col] : 0.f;
     wait_vmcnt<0>();   // this wave's part of M (and M') has landed
     store_h();
     f32x16 h2;
-    mix3<false, NT>(c1, chi, clo, mt, wave, lane, col, h2);   // H2 = C1 M (its first barrier publishes M)
+    mix3<false, NW>(c1, chi, clo, mt, wave, lane, col, h2);   // H2 = C1 M (its first barrier publishes M)
     float c2[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) c2[v] = cv ? act_value<F, true>(h2[v] * w2 + p2) : 0.f;
     if constexpr (L == 3) {
-        const float w3 = cv ? a.w3[q.c0 + col] : 0.f, p3 = cv ? a.p3[q.c0 + col] : 0.f;
         f32x16 h3;
-        mix3<false, NT>(c2, chi, clo, mt2, wave, lane, col, h3);   // H3 = C2 M'
+        mix3<false, NW>(c2, chi, clo, mt2, wave, lane, col, h3);   // H3 = C2 M'
 #pragma unroll
         for (int v = 0; v < 16; ++v) c2[v] = cv ? act_value<F, true>(h3[v] * w3 + p3) : 0.f;
     }
@@ -608,18 +630,20 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_fwd_kernel(BranchArgs
 // parts, as the forward does (so the cosine arguments are the forward's);
 // the gradient mixing products (dC1 = dH2 M^T, dC2 = dH3 M'^T) take theirs as
 // a high + low pair.
-template <Act F, int L, int NT>
-__global__ __launch_bounds__(kThreads * NT, 1) void branch_bwd_kernel(BranchArgs a) {
-    static_assert(L != 3 || NT == 1, "the 3-layer form holds both mixing matrices in LDS at r <= 128");
-    __shared__ __attribute__((aligned(1024))) char lds[sk_lds<NT, L>()];
+template <Act F, int L, int NW>
+__global__ __launch_bounds__(64 * SkShape<NW>::WAVES, 1) void branch_bwd_kernel(BranchArgs a) {
+    static_assert(L != 3 || NW <= 4, "the 3-layer form holds both mixing matrices in LDS at r <= 128");
+    using S = SkShape<NW>;
+    __shared__ __attribute__((aligned(1024))) char lds[S::lds(L)];
     char* mt = lds;
-    char* mt2 = mt + NT * NT * kSkM;   // 3-layer form
-    char* chi = mt + (L == 3 ? 2 : 1) * NT * NT * kSkM;
-    char* clo = chi + NT * kSkC;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    char* mt2 = mt + S::NT * S::NT * S::MT;   // 3-layer form
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, h = lane >> 5;
-    if (!chain_live(a)) return;
-    const ChainPos q = chain_pos(a);
+    if (!chain_live<NW>(a)) return;
+    const int tb = wid / NW, wave = wid % NW;   // token block of the workgroup, 32 rank columns
+    const ChainPos q = chain_pos<NW>(a, tb);
+    char* chi = mt + (L == 3 ? 2 : 1) * S::NT * S::NT * S::MT + 2 * tb * S::CT;
+    char* clo = chi + S::CT;
     const int r = a.r, R = a.R;
     // targets of the frequency / phase gradient sums
     float* gw1 = a.dw1;
@@ -639,8 +663,8 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_bwd_kernel(BranchArgs
         gp3 = c + 5 * arr;
     }
 
-    if constexpr (L >= 2) m_dma<NT>(a.M + (int64_t)q.g * r * r, r, mt, wave, lane);
-    if constexpr (L == 3) m_dma<NT>(a.M2 + (int64_t)q.g * r * r, r, mt2, wave, lane);
+    if constexpr (L >= 2) m_dma<NW>(a.M + (int64_t)q.g * r * r, r, mt, wid, lane);
+    if constexpr (L == 3) m_dma<NW>(a.M2 + (int64_t)q.g * r * r, r, mt2, wid, lane);
     const int col = 32 * wave + r32;
     const bool cv = col < r;
     const int gc = q.c0 + col;   // column of the [R] vectors
@@ -667,6 +691,9 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_bwd_kernel(BranchArgs
 
     // H from the reserve (rows past T and columns past r read as zero),
     // issued before the partial sums so that both arrive in one round trip
+    const float w1 = rank_vec(a, a.w1, q, col), p1 = rank_vec(a, a.p1, q, col);
+    const float w2 = L >= 2 ? rank_vec(a, a.w2, q, col) : 0.f, p2 = L >= 2 ? rank_vec(a, a.p2, q, col) : 0.f;
+    const float w3 = L == 3 ? rank_vec(a, a.w3, q, col) : 0.f, p3 = L == 3 ? rank_vec(a, a.p3, q, col) : 0.f;
     float hr[16], d1[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v)
@@ -674,7 +701,6 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_bwd_kernel(BranchArgs
     f32x16 dc2;
     sum_partials(a, q.row0, q.c0, col, h, dc2);   // the output's gradient dy W_up^T
     // A1 = H w1 + p1, keep f'(A1)
-    const float w1 = cv ? a.w1[gc] : 0.f, p1 = cv ? a.p1[gc] : 0.f;
     float c1[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -694,7 +720,6 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_bwd_kernel(BranchArgs
             dc1[v] = dc2[v];
         }
     } else {
-        const float w2 = cv ? a.w2[gc] : 0.f, p2 = cv ? a.p2[gc] : 0.f;
         const __amdgpu_buffer_rsrc_t rc1 = pair_rsrc(a.C1s), rdh2 = pair_rsrc(a.dH2s);
         wait_vmcnt<0>();   // this wave's part of M (and M') has landed
         // C1's pair (for dM) to scratch; the barrier in mix3 publishes M
@@ -704,7 +729,7 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_bwd_kernel(BranchArgs
             store_pair(rc1, v, c.hi, c.lo);
         }
         f32x16 h2;
-        mix3<false, NT>(c1, chi, clo, mt, wave, lane, col, h2);   // H2 = C1 M
+        mix3<false, NW>(c1, chi, clo, mt, wave, lane, col, h2);   // H2 = C1 M
         // A2 = H2 w2 + p2: C2 = f(A2), keep f'(A2)
         float c2[16], d2[16];
 #pragma unroll
@@ -724,7 +749,6 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_bwd_kernel(BranchArgs
         } else {
             // the third layer: H3 = C2 M', A3 = H3 w3 + p3, C3 = f(A3);
             // dA3 = f'(A3) dC3, dH3 = dA3 w3, dC2 = dH3 M'^T
-            const float w3 = cv ? a.w3[gc] : 0.f, p3 = cv ? a.p3[gc] : 0.f;
             const __amdgpu_buffer_rsrc_t rc2m = pair_rsrc(a.C2ms), rdh3 = pair_rsrc(a.dH3s);
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -732,7 +756,7 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_bwd_kernel(BranchArgs
                 store_pair(rc2m, v, c.hi, c.lo);
             }
             f32x16 h3;
-            mix3<false, NT>(c2, chi, clo, mt2, wave, lane, col, h3);
+            mix3<false, NW>(c2, chi, clo, mt2, wave, lane, col, h3);
             float da3h3[16], da3[16];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -758,7 +782,7 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_bwd_kernel(BranchArgs
             __syncthreads();   // dH3 tiles complete
 #pragma unroll
             for (int v = 0; v < 16; ++v) dcm[v] = 0.f;
-            mix_mma<true, NT>(chi, clo, mt2, wave, lane, dcm);   // dC2 = dH3 M'^T
+            mix_mma<true, NW>(chi, clo, mt2, wave, lane, dcm);   // dC2 = dH3 M'^T
             __syncthreads();                                      // done reading the dH3 tiles
         }
 
@@ -786,7 +810,7 @@ __global__ __launch_bounds__(kThreads * NT, 1) void branch_bwd_kernel(BranchArgs
 
 #pragma unroll
         for (int v = 0; v < 16; ++v) dc1[v] = 0.f;
-        mix_mma<true, NT>(chi, clo, mt, wave, lane, dc1);   // dC1 = dH2 M^T
+        mix_mma<true, NW>(chi, clo, mt, wave, lane, dc1);   // dC1 = dH2 M^T
     }
 
     // dA1 = f'(A1) dC1; dw1 += dA1 H, dp1 += dA1; dH = dA1 w1

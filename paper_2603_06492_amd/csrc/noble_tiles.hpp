@@ -32,13 +32,11 @@ __device__ __forceinline__ int lds_off(int row, int chunk) {
     return row * kRowBytes + ((chunk ^ ((row ^ (row >> 3)) & 7)) << 4);
 }
 
-// bf16 <-> f32 (bf16 kept as raw uint16 bits).  Round to nearest even.
+// bf16 <-> f32 (bf16 kept as raw uint16 bits).  Round to nearest even, by the
+// conversion instruction: the same bits as rounding in integers (compared for
+// all 2^32 inputs) in one instruction instead of six.
 __device__ __forceinline__ float bf2f(uint32_t h) { return __uint_as_float(h << 16); }
-__device__ __forceinline__ uint32_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
+__device__ __forceinline__ uint32_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 template <typename E> __device__ __forceinline__ E to_elt(float f);
 template <> __device__ __forceinline__ uint16_t to_elt<uint16_t>(float f) { return (uint16_t)f2bf(f); }
 template <> __device__ __forceinline__ float to_elt<float>(float f) { return f; }
