@@ -387,7 +387,7 @@ FwdPlan plan_fwd(const noble_linear_desc* d) {
     for (int i = kTile256x128; i < kTileIds; ++i) {
         const TileCost& t = kTileCost[i];
         const int64_t tiles = (T + t.bm - 1) / t.bm * ((d->d_out + t.bn - 1) / t.bn + (R + t.bn - 1) / t.bn);
-        for (int s = 1; s <= 4 && (s == 1 || kPjMinChunks * s <= nk1); ++s) {
+        for (int s = 1; s <= 4 && kPjMinChunks * s <= nk1; ++s) {
             if (split_need(d, s) > kStaticScratchBytes || tiles * s >= (1 << 22)) break;
             const double c = std::max(tile_time(t, tiles * s, cdiv(nk1, s)), hbm) +
                              2.0 * s * (double)T * (double)(d->d_out + R) * 4 / kPartBytesPerUs + kFinFixed;
