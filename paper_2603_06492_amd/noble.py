@@ -2,8 +2,10 @@
 
 Every step of the layer runs in the HIP kernels of ``libnoble.so``; this module
 only checks tensors, passes their device pointers and the current HIP stream,
-and turns status codes into exceptions.  There is no fallback: if the library
-is not built, or the device is not gfx950, calls raise.
+and turns status codes into exceptions.  Well-formed calls do that in native
+code (``_noble_torch.so``); the Python code here serves the others and raises
+the errors.  There is no fallback of the computation: if the libraries are not
+built, or the device is not gfx950, calls raise.
 
 Functions keep the C names: ``noble_linear_workspace_size``,
 ``noble_linear_fwd_scratch_size``,
@@ -20,11 +22,13 @@ names in ``ACTIVATIONS``; the default is the CosNet.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional, Tuple
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG_DIR, "libnoble.so")
+BINDING_PATH = os.path.join(PKG_DIR, "_noble_torch.so")
 
 NOBLE_BF16 = 0
 NOBLE_F32 = 1
@@ -59,6 +63,7 @@ ACTIVATIONS = {
 LAYERS = {"cosnet": 2, "cos": 1, "tanh": 1, "tanh_m": 2, "leaky_relu": 1, "leaky_relu_m": 2, "gelu": 1,
           "gelu_m": 2, "cosnet3": 3}
 TWO_LAYER = {n for n, k in LAYERS.items() if k >= 2}
+_LAYERS_OF_CODE = {ACTIVATIONS[n]: k for n, k in LAYERS.items()}
 
 
 def activation_code(activation) -> int:
@@ -74,10 +79,9 @@ def layers(activation) -> int:
     """Applications of the nonlinearity: 1, 2 (CosNet and the _m names) or 3
     (the 3-layer CosNet)."""
     code = activation_code(activation)
-    for n, c in ACTIVATIONS.items():
-        if c == code:
-            return LAYERS[n]
-    raise ValueError(f"unknown activation code {code}")
+    if code not in _LAYERS_OF_CODE:
+        raise ValueError(f"unknown activation code {code}")
+    return _LAYERS_OF_CODE[code]
 
 
 def two_layers(activation) -> bool:
@@ -157,6 +161,30 @@ def lib() -> ctypes.CDLL:
                                         ctypes.c_uint64] + [_vp] * 10
         _lib = L
     return _lib
+
+
+_native_module = None
+
+
+def _native():
+    """The binding's native calls (_noble_torch.so), given the library's entry
+    points.  They serve well-formed calls on ordinary tensors and return None
+    for any other, which the Python code below then checks and runs."""
+    global _native_module
+    if _native_module is None:
+        _torch()
+        L = lib()
+        if not os.path.exists(BINDING_PATH):
+            raise RuntimeError(f"{BINDING_PATH} is missing: build it with __graft_entry__.build() "
+                               "(or python -m paper_2603_06492_amd._build)")
+        spec = importlib.util.spec_from_file_location("_noble_torch", BINDING_PATH)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        m.init(*(ctypes.cast(f, _vp).value for f in (
+            L.noble_linear_fwd, L.noble_linear_fwd_static, L.noble_linear_bwd, L.noble_linear_workspace_size,
+            L.noble_linear_fwd_scratch_size)))
+        _native_module = m
+    return _native_module
 
 
 def noble_status_string(status: int) -> str:
@@ -276,6 +304,14 @@ def noble_linear_fwd(x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, re
     [G, r, r], the vectors [G r], W_up [G r, d_out / G] (one branch per block
     of d_out / G output columns).
     """
+    if stream is None:
+        act = activation_code(activation)
+        st = _native().forward(False, act, _LAYERS_OF_CODE.get(act), groups, x, W, b, W_down, omega1, phi1, M, omega2,
+                               phi2, W_up, y, reserve, scratch)
+        if st is not None:
+            if st != 0:
+                raise NobleError(st, "noble_linear_fwd")
+            return
     torch = _torch()
     T, d_in = x.shape
     d_out = W.shape[1]
@@ -305,6 +341,14 @@ def noble_linear_fwd_static(x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up
                             stream=None, activation=0, groups: int = 1) -> None:
     """noble_linear_fwd without a scratch argument: the library's own static
     device scratch (for callers that cannot allocate; see include/noble.h)."""
+    if stream is None:
+        act = activation_code(activation)
+        st = _native().forward(True, act, _LAYERS_OF_CODE.get(act), groups, x, W, b, W_down, omega1, phi1, M, omega2,
+                               phi2, W_up, y, reserve, None)
+        if st is not None:
+            if st != 0:
+                raise NobleError(st, "noble_linear_fwd_static")
+            return
     torch = _torch()
     T, d_in = x.shape
     d_out = W.shape[1]
@@ -336,6 +380,14 @@ def noble_linear_bwd(dy, x, W, W_down, omega1, phi1, M, omega2, phi2, W_up, rese
     accept None for M, omega2, phi2, dM, domega2 and dphi2 (given gradient
     tensors are set to zero).
     """
+    if stream is None:
+        act = activation_code(activation)
+        st = _native().backward(act, _LAYERS_OF_CODE.get(act), groups, dy, x, W, W_down, omega1, phi1, M, omega2, phi2,
+                                W_up, reserve, dx, dW, db, dW_down, dM, dW_up, domega1, dphi1, domega2, dphi2, scratch)
+        if st is not None:
+            if st != 0:
+                raise NobleError(st, "noble_linear_bwd")
+            return
     torch = _torch()
     T, d_in = x.shape
     d_out = W.shape[1]
@@ -472,16 +524,21 @@ def _make_function():
 
         @staticmethod
         def forward(ctx, x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, activation=0, groups=1):
-            T, d_in = x.shape
-            d_out, R = W.shape[1], W_down.shape[1]
-            r = R // groups
-            dt = _dtype_code(x)
             act = activation_code(activation)
-            reserve, scratch = alloc_workspace(T, d_in, d_out, r, dt, x.device, groups=groups, forward_only=True,
-                                               activation=act)
-            y = torch.empty((T, d_out), dtype=x.dtype, device=x.device)
-            noble_linear_fwd(x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, reserve, scratch,
-                             activation=act, groups=groups)
+            out = _native().module_forward(True, act, _LAYERS_OF_CODE.get(act), groups, x, W, b, W_down, omega1, phi1,
+                                           M, omega2, phi2, W_up)
+            if isinstance(out, int):
+                raise NobleError(out, "noble_linear_fwd")
+            if out is not None:
+                y, reserve = out
+            else:
+                T, d_in = x.shape
+                d_out, R = W.shape[1], W_down.shape[1]
+                reserve, scratch = alloc_workspace(T, d_in, d_out, R // groups, _dtype_code(x), x.device,
+                                                   groups=groups, forward_only=True, activation=act)
+                y = torch.empty((T, d_out), dtype=x.dtype, device=x.device)
+                noble_linear_fwd(x, W, b, W_down, omega1, phi1, M, omega2, phi2, W_up, y, reserve, scratch,
+                                 activation=act, groups=groups)
             ctx.save_for_backward(x, W, W_down, omega1, phi1, M, omega2, phi2, W_up, reserve)
             ctx.has_bias = b is not None
             ctx.act = act
@@ -491,30 +548,31 @@ def _make_function():
         @staticmethod
         def backward(ctx, dy):
             x, W, W_down, omega1, phi1, M, omega2, phi2, W_up, reserve = ctx.saved_tensors
-            T, d_in = x.shape
-            d_out, R = W.shape[1], W_down.shape[1]
-            G = ctx.groups
-            sh, r = _branch_shapes(d_in, d_out, R, G, ctx.act)
-            dev, f32 = x.device, torch.float32
-            two = two_layers(ctx.act)
+            G, act = ctx.groups, ctx.act
+            two = two_layers(act)
             dy = dy.contiguous().to(x.dtype)
-            _, scratch = alloc_workspace(T, d_in, d_out, r, _dtype_code(x), dev, groups=G, activation=ctx.act)
-            dx = torch.empty_like(x)
-            g = {n: torch.empty(s, dtype=f32, device=dev) for n, s in (
-                ("dW", (d_in, d_out)), ("db", (d_out,)), ("dW_down", sh["W_down"]), ("dM", sh["M"]),
-                ("dW_up", sh["W_up"]), ("domega1", sh["vec"]), ("dphi1", sh["vec"]), ("domega2", sh["vec2"]),
-                ("dphi2", sh["vec2"]))}
-            if not two:
-                g["dM"] = g["domega2"] = g["dphi2"] = None
-            noble_linear_bwd(dy, x, W, W_down, omega1, phi1, M, omega2, phi2, W_up, reserve,
-                             dx, g["dW"], g["db"], g["dW_down"], g["dM"], g["dW_up"],
-                             g["domega1"], g["dphi1"], g["domega2"], g["dphi2"], scratch, activation=ctx.act,
-                             groups=G)
-            dM = g["dM"].to(M.dtype) if (two and M is not None) else None
+            out = _native().module_backward(ctx.has_bias, act, _LAYERS_OF_CODE.get(act), G, dy, x, W, W_down, omega1,
+                                            phi1, M, omega2, phi2, W_up, reserve)
+            if isinstance(out, int):
+                raise NobleError(out, "noble_linear_bwd")
+            if out is not None:
+                dx, dW, db, dWd, do1, dp1, dM, do2, dp2, dWu = out
+            else:
+                T, d_in = x.shape
+                d_out, R = W.shape[1], W_down.shape[1]
+                sh, r = _branch_shapes(d_in, d_out, R, G, act)
+                dev, f32 = x.device, torch.float32
+                _, scratch = alloc_workspace(T, d_in, d_out, r, _dtype_code(x), dev, groups=G, activation=act)
+                dx = torch.empty_like(x)
+                new = lambda shape: torch.empty(shape, dtype=f32, device=dev)
+                dW, db, dWd, dWu = new((d_in, d_out)), new((d_out,)), new(sh["W_down"]), new(sh["W_up"])
+                do1, dp1 = new(sh["vec"]), new(sh["vec"])
+                dM, do2, dp2 = (new(sh["M"]), new(sh["vec2"]), new(sh["vec2"])) if two else (None,) * 3
+                noble_linear_bwd(dy, x, W, W_down, omega1, phi1, M, omega2, phi2, W_up, reserve, dx, dW, db, dWd, dM,
+                                 dWu, do1, dp1, do2, dp2, scratch, activation=act, groups=G)
             cast = lambda gr, p: None if p is None or gr is None else gr.to(p.dtype)
-            return (dx, g["dW"].to(W.dtype), g["db"] if ctx.has_bias else None, g["dW_down"].to(W_down.dtype),
-                    cast(g["domega1"], omega1), cast(g["dphi1"], phi1), dM, cast(g["domega2"], omega2),
-                    cast(g["dphi2"], phi2), g["dW_up"].to(W_up.dtype), None, None)
+            return (dx, dW.to(W.dtype), db if ctx.has_bias else None, dWd.to(W_down.dtype), cast(do1, omega1),
+                    cast(dp1, phi1), cast(dM, M), cast(do2, omega2), cast(dp2, phi2), dWu.to(W_up.dtype), None, None)
 
     return NobleLinearFunction
 
@@ -570,13 +628,18 @@ def _make_module():
         def _infer(self, x2):
             # Nothing to differentiate: the forward without the reserve, so H
             # is neither written nor kept.
+            act, branch = activation_code(self.activation), self._branch()
+            out = _native().module_forward(False, act, _LAYERS_OF_CODE.get(act), self.groups, x2, self.W, self.b,
+                                           *branch)
+            if isinstance(out, int):
+                raise NobleError(out, "noble_linear_fwd")
+            if out is not None:
+                return out[0]
             T = x2.shape[0]
             _, scratch = alloc_workspace(T, self.d_in, self.d_out, self.r, _dtype_code(x2), x2.device,
-                                         groups=self.groups, forward_only=True,
-                                         activation=activation_code(self.activation))
+                                         groups=self.groups, forward_only=True, activation=act)
             y = torch.empty((T, self.d_out), dtype=x2.dtype, device=x2.device)
-            noble_linear_fwd(x2, self.W, self.b, *self._branch(), y, None, scratch,
-                             activation=activation_code(self.activation), groups=self.groups)
+            noble_linear_fwd(x2, self.W, self.b, *branch, y, None, scratch, activation=act, groups=self.groups)
             return y
 
         def param_groups(self, lr):

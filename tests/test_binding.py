@@ -1,0 +1,95 @@
+"""The binding's native calls: the ones they take give what the Python code
+gives, and every other one reaches the Python code and its errors."""
+
+import numpy as np
+import pytest
+
+from paper_2603_06492_amd import inputs as inp
+from paper_2603_06492_amd import noble
+
+
+def test_native_leaves_other_calls_to_python():
+    """CPU tensors, wrong argument counts and non-tensors return None; the
+    public call then raises its own error."""
+    torch = pytest.importorskip("torch")
+    n = noble._native()
+    x, W = torch.zeros(4, 64), torch.zeros(64, 64)
+    assert n.forward() is None and n.backward() is None
+    assert n.module_forward() is None and n.module_backward() is None
+    none = (None,) * 7
+    assert n.forward(False, 0, 2, 1, x, W, None, *none, x, None, None) is None
+    assert n.forward(False, 0, None, 1, x, W, None, *none, x, None, None) is None
+    assert n.forward(False, 0, 2, 1, "x", W, None, *none, x, None, None) is None
+    with pytest.raises(ValueError, match="must be on the GPU"):
+        noble.noble_linear_fwd(x, W, None, *none, x, None, None)
+
+
+CASES = [("cosnet", 1, 40, "bf16"), ("cosnet", 3, 16, "bf16"), ("gelu", 1, 40, "bf16"), ("cosnet3", 3, 24, "bf16"),
+         ("cosnet", 1, 0, "bf16"), ("cosnet", 1, 24, "f32")]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("act,G,r,dt", CASES, ids=[f"{a}_g{g}_r{r}_{d}" for a, g, r, d in CASES])
+def test_native_equals_python(act, G, r, dt, monkeypatch):
+    """Forward and gradients of the module, with the native calls and without,
+    bit for bit (db and the frequency / phase gradients, summed atomically, to
+    float32 rounding)."""
+    import torch
+    sd = torch.bfloat16 if dt == "bf16" else torch.float32
+    print(f"[binding] {act} groups={G} r={r} {dt}", flush=True)
+    m = noble.NobleLinear(104, 264, r, dtype=sd, activation=act, groups=G, seed=3)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn(2, 37, 104, device="cuda", generator=g).to(sd).requires_grad_(True)
+    dy = torch.randn(2, 37, 264, device="cuda", generator=g).to(sd)
+
+    def step():
+        m.zero_grad(set_to_none=True)
+        x.grad = None
+        y = m(x)
+        y.backward(dy)
+        with torch.no_grad():
+            yi = m(x)
+        return {"y": y.detach(), "yi": yi, "dx": x.grad, **{n: p.grad for n, p in m.named_parameters()}}
+
+    fast = step()
+
+    class Off:
+        def __getattr__(self, name):
+            return lambda *a: None
+
+    native = noble._native()
+    monkeypatch.setattr(noble, "_native_module", Off())
+    slow = step()
+    monkeypatch.setattr(noble, "_native_module", native)
+    assert fast.keys() == slow.keys()
+    for k, a in fast.items():
+        b = slow[k]
+        assert a.shape == b.shape and a.dtype == b.dtype, k
+        if k in ("b", "omega1", "phi1", "omega2", "phi2"):
+            np.testing.assert_allclose(a.double().cpu(), b.double().cpu(), rtol=1e-4,
+                                       atol=1e-5 * float(b.abs().max()), err_msg=k)
+        else:
+            assert torch.equal(a, b), k
+
+
+@pytest.mark.gpu
+def test_errors_stay_the_binding_s():
+    import torch
+    from paper_2603_06492_amd.runner import DeviceProblem
+    p = inp.draw_projection("binding", 16, 64, 64, 8, "bf16", seed=4)
+    dp = DeviceProblem(p)
+    dp.fwd()
+    y = dp.y
+    for bad, err in ((y[:8], ValueError), (y.float(), TypeError), (y.cpu(), ValueError), (y.t(), ValueError)):
+        dp.y = bad
+        with pytest.raises(err):
+            dp.fwd()
+    dp.y = y
+    scratch, dp.scratch = dp.scratch, dp.scratch[:16]
+    with pytest.raises(noble.NobleError):
+        dp.fwd()
+    dp.scratch = scratch
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):   # the current stream of the call
+        dp.fwd()
+    s.synchronize()
