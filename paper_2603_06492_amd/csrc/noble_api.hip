@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "noble.h"
+#include "noble_binding.h"
 #include "noble_finish.hpp"
 #include "noble_gemm_dma.hpp"
 #include "noble_gemm_tile.hpp"
@@ -959,7 +960,10 @@ template <typename E>
 noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x, const void* W, const void* Wd,
                       const float* w1, const float* p1, const void* M, const float* w2, const float* p2,
                       const void* Wu, const void* reserve, void* dx, float* dW, float* db, float* dWd, float* dM,
-                      float* dWu, float* dw1, float* dp1, float* dw2, float* dp2, void* scratch, hipStream_t st) {
+                      float* dWu, float* dw1, float* dp1, float* dw2, float* dp2, void* scratch, hipStream_t st,
+                      bool lowp) {
+    // `lowp` (bf16 path, T > 0): dW, dWd, dM and dWu hold bf16, the float32
+    // sums rounded once where they are stored
     constexpr int BK = Elt<E>::BK;
     constexpr size_t ES = sizeof(E);
     const int64_t T = d->T, din = d->d_in, dout = d->d_out, r = d->r;
@@ -1089,13 +1093,15 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
         ReduceList red{};
         static_assert(kChainCopies <= kMaxReduceSlices, "copies exceed the reduction's slices");
         static_assert(kMaxZero >= kMaxProblems + 6, "the reduction list holds every product and six copies");
-        auto reduce = [&](const float* part, float* out, int64_t n, int S, int fw = 0, int fold = 0) {
+        auto reduce = [&](const float* part, float* out, int64_t n, int S, bool bf16 = false, int fw = 0,
+                          int fold = 0) {
             red.part[red.count] = part;
             red.out[red.count] = out;
             red.n[red.count] = n;
             red.S[red.count] = S;
             red.fw[red.count] = fw;
             red.fold[red.count] = fold;
+            red.bf16[red.count] = bf16 ? 1 : 0;
             ++red.count;
         };
         Batch<GemmBatch> bt;
@@ -1110,22 +1116,26 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
         }
         const Operand xT = operand1(seg(x, din, T), din);
         const Operand dyN = operand1(seg(dy, dout, T), dout);
-        bt.add(xT, dyN, (int)din, (int)dout, nkT, dW, dout, true, nullptr, db, wp.split,
+        bt.add(xT, dyN, (int)din, (int)dout, nkT, dW, dout, wp.split > 1 || !lowp, nullptr, db, wp.split,
                wp.split > 1 ? wpart : nullptr);
-        if (wp.split > 1) reduce(wpart, dW, din * dout, wp.split);
+        if (wp.split > 1) reduce(wpart, dW, din * dout, wp.split, lowp);
         if (r > 0) {
             const int rs = wp.rank;
             float* rp = rpart;
+            // Element n of a storage parameter's gradient.
+            auto at = [&](float* p, int64_t n) {
+                return lowp ? reinterpret_cast<float*>(reinterpret_cast<uint16_t*>(p) + n) : p + n;
+            };
             // One rank product [m, n]: a split product stores its pieces in the
             // next partial slots, as does (for any split) a product over high +
             // low operand pairs, whose output [m, n] the reduction folds into
             // `out` ([m / 2, n] or [m, n / 2] per the fold bits; F = its width).
             auto rank = [&](const Operand& A, const Operand& B, int64_t m, int64_t n, float* out, int fold, int64_t F) {
                 const bool parts = fold != 0 || rs > 1;
-                bt.add(A, B, (int)m, (int)n, nkT, out, n, true, nullptr, nullptr, rs, parts ? rp : nullptr);
+                bt.add(A, B, (int)m, (int)n, nkT, out, n, parts || !lowp, nullptr, nullptr, rs, parts ? rp : nullptr);
                 if (parts) {
                     const int64_t outn = m * n / ((fold & 1 ? 2 : 1) * (fold & 2 ? 2 : 1));
-                    reduce(rp, out, outn, rs, fold ? (int)F : 0, fold);
+                    reduce(rp, out, outn, rs, lowp, fold ? (int)F : 0, fold);
                     rp += (int64_t)rs * m * n;
                 }
             };
@@ -1135,20 +1145,20 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
                 const int64_t c0 = g * r;
                 const Operand C2T = operand1(seg(C2s + c0 * (int64_t)ES, R, T), r);
                 const Operand dyg = operand1(seg(static_cast<const E*>(dy) + g * dog, dout, T), dog);
-                rank(C2T, dyg, r, dog, dWu + c0 * dog, 0, 0);
+                rank(C2T, dyg, r, dog, at(dWu, c0 * dog), 0, 0);
                 if (two) {
                     // dM_g = C1_g^T dH2_g: on the bf16 path over the group's
                     // [hi | lo] column pairs of C1 and dH2 (2r x 2r, both folded)
                     const Operand C1T = operand1(seg(C1s + hl * c0 * (int64_t)ES, hl * R, T), hl * r);
                     const Operand dH2N = operand1(seg(dH2s + hl * c0 * (int64_t)ES, hl * R, T), hl * r);
-                    rank(C1T, dH2N, hl * r, hl * r, dM + g * r * r, hl == 2 ? 3 : 0, r);
+                    rank(C1T, dH2N, hl * r, hl * r, at(dM, g * r * r), hl == 2 ? 3 : 0, r);
                 }
                 if (three) {
                     // dM'_g = C2_g^T dH3_g (the middle layer's output and the
                     // third layer's pre-mixing gradient), stored after dM
                     const Operand C2mT = operand1(seg(C2ms + hl * c0 * (int64_t)ES, hl * R, T), hl * r);
                     const Operand dH3N = operand1(seg(dH3s + hl * c0 * (int64_t)ES, hl * R, T), hl * r);
-                    rank(C2mT, dH3N, hl * r, hl * r, dM + (G + g) * r * r, hl == 2 ? 3 : 0, r);
+                    rank(C2mT, dH3N, hl * r, hl * r, at(dM, (G + g) * r * r), hl == 2 ? 3 : 0, r);
                 }
             }
         }
@@ -1295,14 +1305,16 @@ noble_status noble_linear_fwd_static(const noble_linear_desc* desc, const void* 
                                   kStaticScratchBytes, st);
 }
 
-noble_status noble_linear_bwd(const noble_linear_desc* desc, const void* dy, const void* x, const void* W,
+static noble_status bwd_call(const noble_linear_desc* desc, const void* dy, const void* x, const void* W,
                               const void* W_down, const float* omega1, const float* phi1, const void* M,
                               const float* omega2, const float* phi2, const void* W_up, const void* reserve, void* dx,
                               float* dW, float* db, float* dW_down, float* dM, float* dW_up, float* domega1,
                               float* dphi1, float* domega2, float* dphi2, void* scratch, size_t scratch_bytes,
-                              void* stream) {
+                              void* stream, bool storage) {
     NOBLE_TRY(check_desc(desc));
     NOBLE_TRY(check_grids(desc));
+    const bool lowp = storage && desc->dtype == NOBLE_BF16;
+    if (lowp && desc->T == 0) return NOBLE_ERR_BAD_SHAPE;
     const bool rows = desc->T > 0, br = desc->r > 0;
     NOBLE_TRY(need(dy, rows));
     NOBLE_TRY(need(x, rows));
@@ -1336,9 +1348,30 @@ noble_status noble_linear_bwd(const noble_linear_desc* desc, const void* dy, con
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (desc->dtype == NOBLE_BF16)
         return bwd_impl<uint16_t>(desc, dy, x, W, W_down, omega1, phi1, M, omega2, phi2, W_up, reserve, dx, dW, db,
-                                  dW_down, dM, dW_up, domega1, dphi1, domega2, dphi2, scratch, st);
+                                  dW_down, dM, dW_up, domega1, dphi1, domega2, dphi2, scratch, st, lowp);
     return bwd_impl<float>(desc, dy, x, W, W_down, omega1, phi1, M, omega2, phi2, W_up, reserve, dx, dW, db, dW_down,
-                           dM, dW_up, domega1, dphi1, domega2, dphi2, scratch, st);
+                           dM, dW_up, domega1, dphi1, domega2, dphi2, scratch, st, false);
+}
+
+noble_status noble_linear_bwd(const noble_linear_desc* desc, const void* dy, const void* x, const void* W,
+                              const void* W_down, const float* omega1, const float* phi1, const void* M,
+                              const float* omega2, const float* phi2, const void* W_up, const void* reserve, void* dx,
+                              float* dW, float* db, float* dW_down, float* dM, float* dW_up, float* domega1,
+                              float* dphi1, float* domega2, float* dphi2, void* scratch, size_t scratch_bytes,
+                              void* stream) {
+    return bwd_call(desc, dy, x, W, W_down, omega1, phi1, M, omega2, phi2, W_up, reserve, dx, dW, db, dW_down, dM,
+                    dW_up, domega1, dphi1, domega2, dphi2, scratch, scratch_bytes, stream, false);
+}
+
+noble_status noble_linear_bwd_storage(const noble_linear_desc* desc, const void* dy, const void* x, const void* W,
+                                      const void* W_down, const float* omega1, const float* phi1, const void* M,
+                                      const float* omega2, const float* phi2, const void* W_up, const void* reserve,
+                                      void* dx, void* dW, float* db, void* dW_down, void* dM, void* dW_up,
+                                      float* domega1, float* dphi1, float* domega2, float* dphi2, void* scratch,
+                                      size_t scratch_bytes, void* stream) {
+    auto f = [](void* p) { return static_cast<float*>(p); };
+    return bwd_call(desc, dy, x, W, W_down, omega1, phi1, M, omega2, phi2, W_up, reserve, dx, f(dW), db, f(dW_down),
+                    f(dM), f(dW_up), domega1, dphi1, domega2, dphi2, scratch, scratch_bytes, stream, true);
 }
 
 noble_status noble_profile_next_wgrad(void* start_event, void* stop_event, int64_t* workgroups) {

@@ -77,11 +77,13 @@ struct ReduceList {
     int S[kMaxZero];
     int fw[kMaxZero];          // folded arrays: the output row width F (a multiple of 4)
     int fold[kMaxZero];        // 0, or the fold bits above
+    int bf16[kMaxZero];        // out holds bf16: the float32 sum rounded once
     int first[kMaxZero + 1];   // array s owns blocks first[s] .. first[s + 1] - 1
     int count;
 };
 
 constexpr int kMaxReduceSlices = 16;
+typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 
 // out[i] = part[i] + part[n + i] + ... + part[(S - 1) n + i] for each array,
 // every array on its own range of blocks.  The S loads of an element are
@@ -97,6 +99,14 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceList z) {
     float* o = z.out[s];
     const int64_t n = z.n[s];
     const int S = z.S[s];
+    const bool lowp = z.bf16[s] != 0;
+    auto put = [&](int64_t i, const f32x4& v) {   // elements 4i .. 4i + 3
+        if (lowp)
+            reinterpret_cast<u16x4*>(o)[i] =
+                u16x4{(uint16_t)f2bf(v[0]), (uint16_t)f2bf(v[1]), (uint16_t)f2bf(v[2]), (uint16_t)f2bf(v[3])};
+        else
+            reinterpret_cast<f32x4*>(o)[i] = v;
+    };
     const int64_t stride = (int64_t)(z.first[s + 1] - z.first[s]) * blockDim.x;
     const int64_t gid = (int64_t)(blockIdx.x - z.first[s]) * blockDim.x + threadIdx.x;
     const int64_t n4 = n >> 2;
@@ -122,7 +132,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceList z) {
                 acc += v[2];
                 acc += v[3];
             }
-            reinterpret_cast<f32x4*>(o)[i] = acc;
+            put(i, acc);
         }
         return;
     }
@@ -135,7 +145,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceList z) {
 #pragma unroll
         for (int q = 1; q < kMaxReduceSlices; ++q)
             if (q < S) acc += v[q];
-        reinterpret_cast<f32x4*>(o)[i] = acc;
+        put(i, acc);
     }
     for (int64_t i = (n4 << 2) + gid; i < n; i += stride) {
         float v[kMaxReduceSlices];
@@ -146,7 +156,10 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceList z) {
 #pragma unroll
         for (int q = 1; q < kMaxReduceSlices; ++q)
             if (q < S) acc += v[q];
-        o[i] = acc;
+        if (lowp)
+            reinterpret_cast<uint16_t*>(o)[i] = (uint16_t)f2bf(acc);
+        else
+            o[i] = acc;
     }
 }
 

@@ -25,13 +25,14 @@
 #include <algorithm>
 #include <initializer_list>
 
-#include "noble.h"
+#include "noble_binding.h"
 
 namespace {
 
 decltype(&noble_linear_fwd) p_fwd;
 decltype(&noble_linear_fwd_static) p_fwd_static;
 decltype(&noble_linear_bwd) p_bwd;
+decltype(&noble_linear_bwd_storage) p_bwd_storage;
 decltype(&noble_linear_workspace_size) p_sizes;
 decltype(&noble_linear_fwd_scratch_size) p_fwd_size;
 
@@ -247,14 +248,14 @@ PyObject* module_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
 }
 
 // module_backward(has_bias, act, layers, groups, dy, x, W, W_down, omega1, phi1, M, omega2, phi2, W_up, reserve) ->
-// (dx, dW, db, dW_down, domega1, dphi1, dM, domega2, dphi2, dW_up) with the parameter gradients in float32 (None for
-// those the form does not have), a status, or None.
+// (dx, dW, db, dW_down, domega1, dphi1, dM, domega2, dphi2, dW_up), dW, dW_down, dM and dW_up in the storage dtype and
+// the vectors in float32 (None for those the form does not have), a status, or None.
 PyObject* module_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     if (n != 15) Py_RETURN_NONE;
     const bool bias = a[0] == Py_True;
     Call c(a[1], a[2], a[3], a[5], a[6], a[7]);
-    if (!c.ok || a[7] == Py_None) Py_RETURN_NONE;
+    if (!c.ok || a[7] == Py_None || c.T == 0) Py_RETURN_NONE;
     const void* dy = c.ptr(a[4], c.sd, {c.T, c.dout});
     const void* x = c.ptr(a[5], c.sd, {c.T, c.din});
     const void* W = c.ptr(a[6], c.sd, {c.din, c.dout});
@@ -270,9 +271,9 @@ PyObject* module_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const auto f32 = at::kFloat;
         const at::Tensor scratch = c.work(scr);
         g[0] = c.empty({c.T, c.din}, c.sd);
-        g[1] = c.empty({c.din, c.dout}, f32);
+        g[1] = c.empty({c.din, c.dout}, c.sd);
         if (bias) g[2] = c.empty({c.dout}, f32);
-        g[3] = c.empty({c.din, c.R}, f32);
+        g[3] = c.empty({c.din, c.R}, c.sd);
         g[4] = c.empty({c.R}, f32);
         g[5] = c.empty({c.R}, f32);
         if (c.layers >= 2) {
@@ -282,13 +283,14 @@ PyObject* module_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
             if (c.G > 1) ms.push_back(c.G);
             ms.push_back(c.r);
             ms.push_back(c.r);
-            g[6] = c.empty(ms, f32);
+            g[6] = c.empty(ms, c.sd);
             for (int i : {7, 8}) g[i] = three ? c.empty({2, c.R}, f32) : c.empty({c.R}, f32);
         }
-        g[9] = c.empty({c.R, c.dog}, f32);
-        auto f = [&](int i) { return g[i].defined() ? static_cast<float*>(g[i].data_ptr()) : nullptr; };
-        st = p_bwd(&c.d, dy, x, W, p.Wd, p.o1, p.p1, p.M, p.o2, p.p2, p.Wu, reserve, g[0].data_ptr(), f(1), f(2), f(3),
-                   f(6), f(9), f(4), f(5), f(7), f(8), scratch.data_ptr(), (size_t)scratch.numel(), c.stream());
+        g[9] = c.empty({c.R, c.dog}, c.sd);
+        auto v = [&](int i) { return g[i].defined() ? g[i].data_ptr() : nullptr; };
+        auto f = [&](int i) { return static_cast<float*>(v(i)); };
+        st = p_bwd_storage(&c.d, dy, x, W, p.Wd, p.o1, p.p1, p.M, p.o2, p.p2, p.Wu, reserve, v(0), v(1), f(2), v(3),
+                           v(6), v(9), f(4), f(5), f(7), f(8), scratch.data_ptr(), (size_t)scratch.numel(), c.stream());
     }
     if (st != NOBLE_OK) return PyLong_FromLong(st);
     PyObject* out = PyTuple_New(10);
@@ -301,15 +303,16 @@ PyObject* module_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// init(fwd, fwd_static, bwd, workspace_size, fwd_scratch_size): the library's entry points, as addresses.
+// init(fwd, fwd_static, bwd, bwd_storage, workspace_size, fwd_scratch_size): the library's entry points, as addresses.
 PyObject* init(PyObject*, PyObject* args) {
-    unsigned long long p[5];
-    if (!PyArg_ParseTuple(args, "KKKKK", &p[0], &p[1], &p[2], &p[3], &p[4])) return nullptr;
+    unsigned long long p[6];
+    if (!PyArg_ParseTuple(args, "KKKKKK", &p[0], &p[1], &p[2], &p[3], &p[4], &p[5])) return nullptr;
     p_fwd = reinterpret_cast<decltype(p_fwd)>(p[0]);
     p_fwd_static = reinterpret_cast<decltype(p_fwd_static)>(p[1]);
     p_bwd = reinterpret_cast<decltype(p_bwd)>(p[2]);
-    p_sizes = reinterpret_cast<decltype(p_sizes)>(p[3]);
-    p_fwd_size = reinterpret_cast<decltype(p_fwd_size)>(p[4]);
+    p_bwd_storage = reinterpret_cast<decltype(p_bwd_storage)>(p[3]);
+    p_sizes = reinterpret_cast<decltype(p_sizes)>(p[4]);
+    p_fwd_size = reinterpret_cast<decltype(p_fwd_size)>(p[5]);
     Py_RETURN_NONE;
 }
 

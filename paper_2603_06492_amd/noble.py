@@ -181,8 +181,8 @@ def _native():
         m = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(m)
         m.init(*(ctypes.cast(f, _vp).value for f in (
-            L.noble_linear_fwd, L.noble_linear_fwd_static, L.noble_linear_bwd, L.noble_linear_workspace_size,
-            L.noble_linear_fwd_scratch_size)))
+            L.noble_linear_fwd, L.noble_linear_fwd_static, L.noble_linear_bwd, L.noble_linear_bwd_storage,
+            L.noble_linear_workspace_size, L.noble_linear_fwd_scratch_size)))
         _native_module = m
     return _native_module
 

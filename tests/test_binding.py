@@ -24,23 +24,26 @@ def test_native_leaves_other_calls_to_python():
         noble.noble_linear_fwd(x, W, None, *none, x, None, None)
 
 
-CASES = [("cosnet", 1, 40, "bf16"), ("cosnet", 3, 16, "bf16"), ("gelu", 1, 40, "bf16"), ("cosnet3", 3, 24, "bf16"),
-         ("cosnet", 1, 0, "bf16"), ("cosnet", 1, 24, "f32")]
+# 1250 rows per batch entry: dW and the rank products split over K, so that the
+# reduction stores their gradients; 37: the products themselves store dW and dW_up
+CASES = [("cosnet", 1, 40, "bf16", 37), ("cosnet", 3, 16, "bf16", 37), ("gelu", 1, 40, "bf16", 37),
+         ("cosnet3", 3, 24, "bf16", 37), ("cosnet", 1, 0, "bf16", 37), ("cosnet", 1, 24, "f32", 37),
+         ("cosnet", 1, 64, "bf16", 1250), ("cosnet", 3, 32, "bf16", 1250), ("cosnet", 1, 0, "bf16", 1250)]
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("act,G,r,dt", CASES, ids=[f"{a}_g{g}_r{r}_{d}" for a, g, r, d in CASES])
-def test_native_equals_python(act, G, r, dt, monkeypatch):
+@pytest.mark.parametrize("act,G,r,dt,n", CASES, ids=[f"{a}_g{g}_r{r}_{d}_{n}" for a, g, r, d, n in CASES])
+def test_native_equals_python(act, G, r, dt, n, monkeypatch):
     """Forward and gradients of the module, with the native calls and without,
     bit for bit (db and the frequency / phase gradients, summed atomically, to
     float32 rounding)."""
     import torch
     sd = torch.bfloat16 if dt == "bf16" else torch.float32
-    print(f"[binding] {act} groups={G} r={r} {dt}", flush=True)
+    print(f"[binding] {act} groups={G} r={r} {dt} {n}", flush=True)
     m = noble.NobleLinear(104, 264, r, dtype=sd, activation=act, groups=G, seed=3)
     g = torch.Generator(device="cuda").manual_seed(5)
-    x = torch.randn(2, 37, 104, device="cuda", generator=g).to(sd).requires_grad_(True)
-    dy = torch.randn(2, 37, 264, device="cuda", generator=g).to(sd)
+    x = torch.randn(2, n, 104, device="cuda", generator=g).to(sd).requires_grad_(True)
+    dy = torch.randn(2, n, 264, device="cuda", generator=g).to(sd)
 
     def step():
         m.zero_grad(set_to_none=True)
