@@ -687,29 +687,6 @@ noble_status launch_dense(const Batch<DenseBatch>& bt, TileId tile, hipStream_t 
     }
 }
 
-// The last launch of a split forward (noble_finish.hpp).
-noble_status launch_finish(const noble_linear_desc* d, const float* P, int S, const void* C2s, const void* Wu,
-                           const float* b, void* y, hipStream_t st) {
-    FinishArgs a{};
-    a.P = P;
-    a.pstride = d->T * d->d_out;
-    a.C2s = static_cast<const uint16_t*>(C2s);
-    a.Wu = static_cast<const uint16_t*>(Wu);
-    a.b = b;
-    a.y = static_cast<uint16_t*>(y);
-    a.T = (int)d->T;
-    a.S = S;
-    a.G = ngroups(d);
-    a.r = (int)d->r;
-    a.R = (int)rank_total(d);
-    a.dog = (int)group_dout(d);
-    a.dout = (int)d->d_out;
-    const dim3 grid((unsigned)((int64_t)cdiv(a.T, kFinRows) * a.G * cdiv(a.dog, kFinCols))), block(256);
-    if (a.r <= 64) return launch(y_finish_kernel<1>, grid, block, st, a);
-    if (a.r <= 128) return launch(y_finish_kernel<2>, grid, block, st, a);
-    return launch(y_finish_kernel<4>, grid, block, st, a);
-}
-
 // Empty batch for y or dx, G problems [M, N] of nk chunks each.
 template <typename E>
 Batch<DenseBatch> dense_batch(int64_t G, int64_t M, int64_t N, int nk, TileId& tile) {
@@ -779,8 +756,7 @@ noble_status launch_proj(bool fwd, const noble_linear_desc* d, const void* A, co
 
 // bf16 path, step 2: the branch nonlinearity (forward or backward) from the
 // summed partials, one workgroup per (32 tokens, group).
-noble_status launch_branch(bool fwd, const noble_linear_desc* d, const ChainArgs& c, const float* P, int S,
-                           hipStream_t st, float* copies = nullptr) {
+BranchArgs branch_args(const noble_linear_desc* d, const ChainArgs& c, const float* P, int S, float* copies = nullptr) {
     BranchArgs a{};
     a.copies = copies;
     a.P = P;
@@ -811,6 +787,11 @@ noble_status launch_branch(bool fwd, const noble_linear_desc* d, const ChainArgs
     a.r = (int)d->r;
     a.G = ngroups(d);
     a.R = (int)rank_total(d);
+    return a;
+}
+noble_status launch_branch(bool fwd, const noble_linear_desc* d, const ChainArgs& c, const float* P, int S,
+                           hipStream_t st, float* copies = nullptr) {
+    const BranchArgs a = branch_args(d, c, P, S, copies);
     return with_act(d->activation, [&]<Act F, int L>() -> noble_status {
         auto run = [&]<int NW>() -> noble_status {
             using Sh = SkShape<NW>;
@@ -824,6 +805,44 @@ noble_status launch_branch(bool fwd, const noble_linear_desc* d, const ChainArgs
         if constexpr (L != 3) return run.template operator()<8>();   // the 3-layer form is validated to r <= 128
         return NOBLE_ERR_BAD_SHAPE;
     });
+}
+
+// The launches of a split forward after its products (noble_finish.hpp): the
+// chain and the finish, in one kernel where its workgroups all run at once
+// (chain_finish_kernel's LDS lets two share a CU, one in the 3-layer form;
+// beyond, the copies of the chain would cost more than the launch they save).
+// Two launches / one, whole calls with cold weights (us): 1 x 2048 -> 6144
+// (48 workgroups) 20.1 / 18.2, 16 x 2048 -> 8192 (64) 22.7 / 20.5, 300 x 2048
+// -> 2048 (160) 22.9 / 20.5, 777 x 8192 -> 2048 (400) 57.8 / 55.4, 500 x 1024
+// -> 4096 (512) 25.6 / 25.4.
+noble_status launch_finish(const noble_linear_desc* d, const ChainArgs& c, const float* Ph, const float* P, int S,
+                           const void* Wu, const float* b, void* y, hipStream_t st) {
+    FinishArgs a{};
+    a.P = P;
+    a.pstride = d->T * d->d_out;
+    a.C2s = reinterpret_cast<const uint16_t*>(c.C2s);
+    a.Wu = static_cast<const uint16_t*>(Wu);
+    a.b = b;
+    a.y = static_cast<uint16_t*>(y);
+    a.T = (int)d->T;
+    a.S = S;
+    a.G = ngroups(d);
+    a.r = (int)d->r;
+    a.R = (int)rank_total(d);
+    a.dog = (int)group_dout(d);
+    a.dout = (int)d->d_out;
+    const int64_t blocks = (int64_t)cdiv(a.T, kFinRows) * a.G * cdiv(a.dog, kFinCols);
+    const dim3 grid((unsigned)blocks), block(256);
+    if (a.r <= 128 && blocks <= (act_layers(d->activation) == 3 ? 256 : 512)) {
+        const ChainFinishArgs cf{branch_args(d, c, Ph, S), a};
+        return with_act(d->activation, [&]<Act F, int L>() -> noble_status {
+            return launch(chain_finish_kernel<F, L>, grid, block, st, cf);
+        });
+    }
+    NOBLE_TRY(launch_branch(true, d, c, Ph, S, st));
+    if (a.r <= 64) return launch(y_finish_kernel<1>, grid, block, st, a);
+    if (a.r <= 128) return launch(y_finish_kernel<2>, grid, block, st, a);
+    return launch(y_finish_kernel<4>, grid, block, st, a);
 }
 
 // K chunk of the large products (128 bytes of a row: 64 bf16 or 32 f32).
@@ -923,8 +942,7 @@ noble_status fwd_impl(const noble_linear_desc* d, const void* x, const void* W, 
                 bt.add(X, operand1(seg(Wd, R, din), R), (int)T, (int)R, nk, nullptr, R, true, nullptr, nullptr,
                        fp.split, P);
                 NOBLE_TRY((launch_dense<E, false>(bt, fp.tile, st)));
-                NOBLE_TRY(launch_branch(true, d, a, P, fp.split, st));
-                return launch_finish(d, Py, fp.split, C2s, Wu, b, y, st);
+                return launch_finish(d, a, P, Py, fp.split, Wu, b, y, st);
             }
             const int S = proj_split(T, din, proj_jobs(d));
             NOBLE_TRY(launch_proj(true, d, x, Wd, P, S, st));

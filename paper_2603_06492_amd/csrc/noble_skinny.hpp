@@ -533,7 +533,7 @@ __device__ __forceinline__ void mix3(const float (&pv)[16], char* chi, char* clo
     __syncthreads();   // done reading the tiles
 }
 
-// Forward chain.  L = 2: the two-application form with M (CosNet for F =
+// Forward chain of a wave's 32 x 32 block: c = the branch output of H = hv.  L = 2: the two-application form with M (CosNet for F =
 // Cos); L = 1: C2 = f(H w1 + p1), M, w2, p2 not read; L = 3 (the 3-layer
 // CosNet): C3 = f((C2 M') w3 + p3) after the second layer, M' = a.M2.  Each
 // mixing operand (C1, and C2 in the 3-layer form) enters the MFMAs as three
@@ -541,6 +541,39 @@ __device__ __forceinline__ void mix3(const float (&pv)[16], char* chi, char* clo
 // then the low part from the first tile again), so every mixing product is
 // as accurate as a float32 one and the cosine arguments carry float32
 // rounding only.
+// Waits for the wave's part of M (and M') in the mixing forms.  `store_h` (H to
+// the reserve) runs after that wait, because stores count in vmcnt.
+struct ChainVec {
+    float w1, p1, w2, p2, w3, p3;   // the lane's column of the frequencies and phases
+};
+template <int L>
+__device__ __forceinline__ ChainVec chain_vec(const BranchArgs& a, const ChainPos& q, int col) {
+    auto get = [&](const float* v, bool used) { return used ? rank_vec(a, v, q, col) : 0.f; };
+    return ChainVec{get(a.w1, true), get(a.p1, true), get(a.w2, L >= 2), get(a.p2, L >= 2), get(a.w3, L == 3),
+                    get(a.p3, L == 3)};
+}
+template <Act F, int L, int NW, typename StoreH>
+__device__ __forceinline__ void chain_fwd(const f32x16& hv, const ChainVec& w, bool cv, char* chi, char* clo,
+                                          const char* mt, const char* mt2, int wave, int lane, int col,
+                                          StoreH store_h, float (&c)[16]) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) c[v] = cv ? act_value<F, true>(hv[v] * w.w1 + w.p1) : 0.f;
+    if constexpr (L >= 2) wait_vmcnt<0>();
+    store_h();
+    if constexpr (L >= 2) {
+        f32x16 h2;
+        mix3<false, NW>(c, chi, clo, mt, wave, lane, col, h2);   // H2 = C1 M (its first barrier publishes M)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) c[v] = cv ? act_value<F, true>(h2[v] * w.w2 + w.p2) : 0.f;
+    }
+    if constexpr (L == 3) {
+        f32x16 h3;
+        mix3<false, NW>(c, chi, clo, mt2, wave, lane, col, h3);   // H3 = C2 M'
+#pragma unroll
+        for (int v = 0; v < 16; ++v) c[v] = cv ? act_value<F, true>(h3[v] * w.w3 + w.p3) : 0.f;
+    }
+}
+
 template <Act F, int L, int NW>
 __global__ __launch_bounds__(64 * SkShape<NW>::WAVES, 1) void branch_fwd_kernel(BranchArgs a) {
     static_assert(L != 3 || NW <= 4, "the 3-layer form holds both mixing matrices in LDS at r <= 128");
@@ -563,10 +596,7 @@ __global__ __launch_bounds__(64 * SkShape<NW>::WAVES, 1) void branch_fwd_kernel(
     // acc[v]: token row0 + 8(v/4) + 4h + v%4, rank column 32 wave + r32 of the group
     const int col = 32 * wave + r32;
     const bool cv = col < r;
-    // the frequencies and phases arrive with the partials, in one round trip
-    const float w1 = rank_vec(a, a.w1, q, col), p1 = rank_vec(a, a.p1, q, col);
-    const float w2 = L >= 2 ? rank_vec(a, a.w2, q, col) : 0.f, p2 = L >= 2 ? rank_vec(a, a.p2, q, col) : 0.f;
-    const float w3 = L == 3 ? rank_vec(a, a.w3, q, col) : 0.f, p3 = L == 3 ? rank_vec(a, a.p3, q, col) : 0.f;
+    const ChainVec w = chain_vec<L>(a, q, col);   // arrives with the partials, in one round trip
     f32x16 acc;
     sum_partials(a, q.row0, q.c0, col, h, acc);
 
@@ -579,39 +609,16 @@ __global__ __launch_bounds__(64 * SkShape<NW>::WAVES, 1) void branch_fwd_kernel(
     // H is read again only by the backward, after every other projection's
     // forward: it is stored non-temporal, so that it does not linger dirty in
     // the memory-side cache.
-    // Stores count in vmcnt: in the mixing forms H is stored after the
-    // barrier, whose wait for M would otherwise also wait for them.
     auto store_h = [&]() {
         if (keep_h)
 #pragma unroll
             for (int v = 0; v < 16; ++v)
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[v]), rh, vo4, soff(v, 4), kStoreNT);
     };
-    float c1[16];
+    float c[16];
+    chain_fwd<F, L, NW>(acc, w, cv, chi, clo, mt, mt2, wave, lane, col, store_h, c);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) c1[v] = cv ? act_value<F, true>(acc[v] * w1 + p1) : 0.f;
-    if constexpr (L == 1) {
-        store_h();
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)f2bf(c1[v]), rc, vo2, soff(v, 2), 0);
-        return;
-    }
-    wait_vmcnt<0>();   // this wave's part of M (and M') has landed
-    store_h();
-    f32x16 h2;
-    mix3<false, NW>(c1, chi, clo, mt, wave, lane, col, h2);   // H2 = C1 M (its first barrier publishes M)
-    float c2[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) c2[v] = cv ? act_value<F, true>(h2[v] * w2 + p2) : 0.f;
-    if constexpr (L == 3) {
-        f32x16 h3;
-        mix3<false, NW>(c2, chi, clo, mt2, wave, lane, col, h3);   // H3 = C2 M'
-#pragma unroll
-        for (int v = 0; v < 16; ++v) c2[v] = cv ? act_value<F, true>(h3[v] * w3 + p3) : 0.f;
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)f2bf(c2[v]), rc, vo2, soff(v, 2), 0);
+    for (int v = 0; v < 16; ++v) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)f2bf(c[v]), rc, vo2, soff(v, 2), 0);
 }
 
 // Backward chain, same forms as branch_fwd_kernel.  The one-application form

@@ -10,7 +10,7 @@ import oracle
 from paper_2603_06492_amd import inputs as inp
 from paper_2603_06492_amd import noble
 
-from _parity import TOL, row_err
+from _parity import TOL, oracle_outputs, row_err
 from test_abi import _align, _proj_split
 
 CASES = [
@@ -42,6 +42,27 @@ def test_forward_scratch_of_the_split(case):
     assert got in sizes and got > _unsplit_scratch(T, di, do, r, G)
     res, full = noble.noble_linear_workspace_size(T, di, do, r, noble.NOBLE_BF16, 0, G)
     assert full >= got
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("act", ["cos", "tanh", "gelu_m", "cosnet3"])
+def test_split_forward_of_other_forms(act):
+    """One, two and three applications where the chain and the finish share a launch, H kept."""
+    import torch
+    from paper_2603_06492_amd.runner import DeviceProblem
+    T, di, do, r, G = 40, 1032, 3 * 136, 56, 3
+    print(f"[split] {act}", flush=True)
+    p = inp.draw_projection("split_" + act, T, di, do, r, "bf16", seed=92, bias_std=0.5, groups=G,
+                            layers=noble.layers(act) if act == "cosnet3" else 2)
+    dp = DeviceProblem(p, canary=True, activation=act)
+    dp.scratch.fill_(255)
+    dp.fwd()
+    torch.cuda.synchronize()
+    assert row_err(dp.y.float().cpu().numpy().astype(np.float64), oracle_outputs(p, activation=act)["y"]) <= TOL["bf16"]
+    h = dp.reserve[:4 * T * G * r].view(torch.float32).view(T, G * r).cpu().numpy()
+    a = p.arrays
+    assert row_err(h, a["x"].astype(np.float64) @ a["W_down"].astype(np.float64)) <= TOL["f32"]
+    assert dp.guards_intact(), "write outside an output buffer"
 
 
 @pytest.mark.gpu
