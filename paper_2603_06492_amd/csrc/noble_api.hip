@@ -307,9 +307,10 @@ bool kpair_tile(int tile, int64_t M, bool bsum) { return tile == 256 && M <= 128
 //   256 x 128   256      0.95,  6               0.75,  6
 //   128 x 128   256      0.60,  5               0.57,  5
 //    64 x 128   512      0.63,  5               0.45,  5
+//    32 x 128   256      0.43,  5.1             0.43,  5.1   (pieces of a split forward)
 // (8192 x 2048 x 2176: 63 / 77 / 102 / 100 us; 2000 x 2048 x 2304: 51 / 34 /
 // 29 / 29 us; 25216 x 768 x 3104: 153 / 148 / 171 / 171 us.)
-enum TileId { kTile256 = 0, kTile256x128, kTile128, kTile64x128, kTileIds };
+enum TileId { kTile256 = 0, kTile256x128, kTile128, kTile64x128, kTile32x128, kTileIds };
 struct TileCost {
     int bm, bn, slots;
     double c_full, e_full, c_part, e_part;
@@ -317,7 +318,8 @@ struct TileCost {
 constexpr TileCost kTileCost[kTileIds] = {{256, 256, 256, 1.50, 11.0, 1.36, 10.0},
                                           {256, 128, 256, 0.95, 6.0, 0.75, 6.0},
                                           {128, 128, 256, 0.60, 5.0, 0.57, 5.0},
-                                          {64, 128, 512, 0.63, 5.0, 0.45, 5.0}};
+                                          {64, 128, 512, 0.63, 5.0, 0.45, 5.0},
+                                          {32, 128, 256, 0.43, 5.1, 0.43, 5.1}};
 double tile_time(const TileCost& t, int64_t blocks, int nk) {
     const int64_t full = blocks / t.slots, rem = blocks % t.slots;
     const double f = nk * t.c_full + t.e_full, p = nk * t.c_part + t.e_part;
@@ -331,7 +333,7 @@ double tile_cost(TileId i, int64_t G, int64_t M, int64_t N, int nk) {
 TileId pick_tile(int64_t G, int64_t M, int64_t N, int nk) {
     TileId best = kTile256;
     double bt = 0;
-    for (int i = 0; i < kTileIds; ++i) {
+    for (int i = 0; i < kTile32x128; ++i) {
         const TileCost& t = kTileCost[i];
         const int64_t blocks = G * ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         if (i > 0 && blocks >= (1 << 22)) continue;   // the dispatch limit is checked for 256 x 256
@@ -354,9 +356,10 @@ TileId pick_tile(int64_t G, int64_t M, int64_t N, int nk) {
 // rule compares both forms by cost: the rank projection (fixed + per chunk)
 // and the tile model of the K-extended product, against the tile model of the
 // pieces (at least the time W takes from HBM), the partials at 5.9 MB per us
-// and the finishing launch.  The chain is in both.  At most 4 pieces: the
-// chain and the finish read four partials in one round trip, and 6 or 8
-// measured slower everywhere; at least four K chunks per piece, as in the rank
+// and the finishing launch.  The chain is in both.  The chain and the finish
+// read four partials in one round trip, so each further four cost 2.1 us: 6 to
+// 12 pieces pay only where a long K meets few tiles (1 x 8192 -> 2048: 4 pieces
+// 27.2 us, 8 23.2).  At least four K chunks per piece, as in the rank
 // projection (shorter pieces gained 2% at most).  Measured over 41 shapes of 1 to 2048 tokens
 // (cold weights, us, unsplit / split): 1 x 2048 -> 6144 37.8 / 22.7,
 // 16 x 2048 -> 8192 37.8 / 24.8, 777 x 8192 -> 2048 94 / 60, 1600 x 4096 ->
@@ -378,7 +381,8 @@ FwdPlan plan_fwd(const noble_linear_desc* d) {
     if (d->dtype != NOBLE_BF16 || d->r == 0 || d->T == 0) return w;
     const int64_t T = d->T, R = rank_total(d), dog = group_dout(d);
     const int G = ngroups(d), nk1 = cdiv(d->d_in, 64), J = proj_jobs(d);
-    constexpr double kProjFixed = 5.3, kProjChunk = 0.24, kFinFixed = 5.4, kPartBytesPerUs = 5.9e6, kHbmBytesPerUs = 4.3e6;
+    constexpr double kProjFixed = 5.3, kProjChunk = 0.24, kFinFixed = 5.4, kPartBytesPerUs = 5.9e6, kHbmBytesPerUs = 4.3e6,
+                     kBatchUs = 2.1;
     const int Sp = proj_split(T, d->d_in, J);
     const int64_t pwaves = ((T + kPjRows - 1) / kPjRows * Sp * J + 255) / 256;
     const int nk = nk1 + cdiv(d->r, 64);
@@ -388,10 +392,12 @@ FwdPlan plan_fwd(const noble_linear_desc* d) {
     for (int i = kTile256x128; i < kTileIds; ++i) {
         const TileCost& t = kTileCost[i];
         const int64_t tiles = (T + t.bm - 1) / t.bm * ((d->d_out + t.bn - 1) / t.bn + (R + t.bn - 1) / t.bn);
-        for (int s = 1; s <= 4 && kPjMinChunks * s <= nk1; ++s) {
+        for (int s : {1, 2, 3, 4, 6, 8, 12}) {
+            if (kPjMinChunks * s > nk1) break;
             if (split_need(d, s) > kStaticScratchBytes || tiles * s >= (1 << 22)) break;
             const double c = std::max(tile_time(t, tiles * s, cdiv(nk1, s)), hbm) +
-                             2.0 * s * (double)T * (double)(d->d_out + R) * 4 / kPartBytesPerUs + kFinFixed;
+                             2.0 * s * (double)T * (double)(d->d_out + R) * 4 / kPartBytesPerUs + kFinFixed +
+                             kBatchUs * ((s + 3) / 4 - 1);
             if (c < best) {
                 best = c;
                 w.tile = (TileId)i;
@@ -675,6 +681,11 @@ noble_status launch_dense(const Batch<DenseBatch>& bt, TileId tile, hipStream_t 
                 return launch(gemm_tile_kernel<true, BKM, 2, 2, 2, 2, 3, false, B>, grid, dim3(256), st, bt.b);
             case kTile64x128:
                 return launch(gemm_tile_kernel<true, BKM, 2, 2, 1, 2, 3, false, B>, grid, dim3(256), st, bt.b);
+            case kTile32x128:
+                // seven stages: a few tokens only wait for W, 96 KB of it in flight per CU
+                if constexpr (!BKM)
+                    return launch(gemm_tile_kernel<true, false, 1, 4, 1, 1, 7, false, B>, grid, dim3(256), st, bt.b);
+                break;
             default: break;
         }
         if (!BKM && plain)

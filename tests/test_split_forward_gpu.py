@@ -23,6 +23,9 @@ CASES = [
     ("T777_r128", 777, 4104, 1032, 128, 1),
     ("T1601_r256", 1601, 2048, 776, 256, 1),
     ("T401_wide", 401, 4096, 3080, 40, 1),
+    # 6 to 12 pieces, 32 x 128 tiles
+    ("T5_deep", 5, 8200, 520, 40, 1),
+    ("T33_deep", 33, 8192, 2048, 128, 1),
 ]
 
 
@@ -35,10 +38,10 @@ def _unsplit_scratch(T, di, do, r, G):
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_forward_scratch_of_the_split(case):
     """These shapes are split: the scratch query holds the float32 partials of
-    x W_down and x W for 1 to 4 pieces."""
+    x W_down and x W for 1 to 12 pieces."""
     _, T, di, do, r, G = case
     got = noble.noble_linear_fwd_scratch_size(T, di, do, r, noble.NOBLE_BF16, 0, G)
-    sizes = [_align(T * G * r * 2) + _align(s * T * G * r * 4) + _align(s * T * do * 4) for s in (1, 2, 3, 4)]
+    sizes = [_align(T * G * r * 2) + _align(s * T * G * r * 4) + _align(s * T * do * 4) for s in (1, 2, 3, 4, 6, 8, 12)]
     assert got in sizes and got > _unsplit_scratch(T, di, do, r, G)
     res, full = noble.noble_linear_workspace_size(T, di, do, r, noble.NOBLE_BF16, 0, G)
     assert full >= got
