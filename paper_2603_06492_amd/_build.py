@@ -15,7 +15,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libnoble.so")
 BINDING = os.path.join(PKG, "_noble_torch.so")
 SOURCES = ["noble_api.hip"]
-HEADERS = ["noble_act.hpp", "noble_init.hpp", "noble_kernels.hpp", "noble_tiles.hpp", "noble_gemm.hpp", "noble_gemm_dma.hpp", "noble_gemm_tile.hpp", "noble_skinny.hpp", "noble_finish.hpp"]
+HEADERS = ["noble_act.hpp", "noble_init.hpp", "noble_kernels.hpp", "noble_tiles.hpp", "noble_gemm.hpp", "noble_gemm_dma.hpp", "noble_gemm_tile.hpp", "noble_skinny.hpp", "noble_finish.hpp", "noble_gemm_f32.hpp", "noble_binding.h", "noble_torch.cpp"]
 
 HIP_FLAGS = [
     "-O3",

@@ -18,6 +18,7 @@
 #include "noble_binding.h"
 #include "noble_finish.hpp"
 #include "noble_gemm_dma.hpp"
+#include "noble_gemm_f32.hpp"
 #include "noble_gemm_tile.hpp"
 #include "noble_init.hpp"
 #include "noble_kernels.hpp"
@@ -659,7 +660,7 @@ noble_status launch_wgrad(const Batch<GemmBatch>& bt, hipStream_t st) {
     if constexpr (sizeof(E) == 2)
         return launch(gemm_bf16_kernel<false, false, true, 0, GemmBatch>, dim3(bt.blocks), dim3(kDmaThreads), st, bt.b);
     else if (bt.bm == 64)
-        return launch(gemm_kernel<E, 64, 64, false, false, true, GemmBatch>, dim3(bt.blocks), dim3(kThreads), st, bt.b);
+        return launch(gemm_f32_kernel<false, false, true, GemmBatch>, dim3(bt.blocks), dim3(kThreads), st, bt.b);
     else
         return launch(gemm_kernel<E, 128, 128, false, false, true, GemmBatch>, dim3(bt.blocks), dim3(kThreads), st,
                       bt.b);
@@ -692,7 +693,7 @@ noble_status launch_dense(const Batch<DenseBatch>& bt, TileId tile, hipStream_t 
             return launch(gemm_bf16_kernel<true, BKM, false, 1, B>, grid, dim3(kDmaThreads), st, bt.b);
         return launch(gemm_bf16_kernel<true, BKM, false, 0, B>, grid, dim3(kDmaThreads), st, bt.b);
     } else if (bt.bm == 64) {
-        return launch(gemm_kernel<E, 64, 64, true, BKM, false, B>, dim3(bt.blocks), dim3(kThreads), st, bt.b);
+        return launch(gemm_f32_kernel<true, BKM, false, B>, dim3(bt.blocks), dim3(kThreads), st, bt.b);
     } else {
         return launch(gemm_kernel<E, 128, 128, true, BKM, false, B>, dim3(bt.blocks), dim3(kThreads), st, bt.b);
     }

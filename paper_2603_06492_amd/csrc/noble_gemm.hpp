@@ -181,13 +181,11 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(Batch batch) {
 #pragma unroll
                     for (int j = 0; j < TN; ++j) mma32<E>(acc[i][j], a[cb][i], b[cb][j]);
                 if constexpr (MORE) {
-                    // a 64-row K-major tile stages in two parts
-                    constexpr int NA = AK && BM < 128 ? 2 : 4, NB = BKM && BN < 128 ? 2 : 4;
-                    if (s < NA) sa.template store_part<NA>(nxt, tid, s);
-                    if (s < NB) sb.template store_part<NB>(nxt + BM * kRowBytes, tid, s);
+                    sa.template store_part<4>(nxt, tid, s);
+                    sb.template store_part<4>(nxt + BM * kRowBytes, tid, s);
                     if constexpr (MORE2) {
-                        if (s < NA) sa.template load_part<NA>(P.A, m0, kc + 2, tid, s);
-                        if (s < NB) sb.template load_part<NB>(P.B, n0, kc + 2, tid, s);
+                        sa.template load_part<4>(P.A, m0, kc + 2, tid, s);
+                        sb.template load_part<4>(P.B, n0, kc + 2, tid, s);
                     }
                 }
                 // Keep each step's staging in its step: the loads of chunk

@@ -24,7 +24,7 @@
 #pragma once
 
 #include "noble_act.hpp"
-#include "noble_gemm.hpp"
+#include "noble_gemm_dma.hpp"
 #include "noble_tiles.hpp"
 
 namespace noble {
@@ -200,11 +200,92 @@ struct ChainShape {
     static constexpr int BK = Elt<E>::BK;
     static constexpr int NKB = RP / BK;     // K chunks of the r x r mixing
     static constexpr int TN = RP / 32;      // 16-wide tiles per wave (waves 2 x 2)
-    static constexpr int MAIN = 2 * (kChainRows + RP) * kRowBytes;
+    static constexpr int NST = 4;           // LDS stages of the rank projection
+    static constexpr int MAIN = NST * (kChainRows + RP) * kRowBytes;
     static constexpr int MIX = NKB * (kChainRows + RP) * kRowBytes;
     static constexpr int LDS = MAIN > MIX ? MAIN : MIX;
     static_assert(RP % BK == 0, "RP must be a multiple of the K chunk");
 };
+
+// The float32 rank projection of 32 tokens, A [T, K] K-major times B [K, r]
+// (BKM: stored [r][K]), all K chunks: acc[0][j] as mma_chunk gives it.  Four
+// waves (2 x 2).  One workgroup's chunks form a chain, and a chunk is 0.1 us
+// of MFMAs, so loads go straight to LDS with three chunks in flight: register
+// staging with one took 0.8 us per chunk.  Layer's forward / backward with
+// register staging and with this (us): 2048 x 768 -> 768, r = 32, 58.7 / 98.8
+// -> 51.7 / 93.0; 64 x 1024 -> 1024, r = 64, 56.2 / 67.8 -> 50.7 / 62.9.
+//  - K-major tiles: rows of 128 B as lds_off lays them out.
+//  - B MN-major: [32 k][4 RP bytes], column n of k-row k at
+//    n ^ 16 ((k / 4) & 3) (& 1 at RP = 32); fragments with four ds_read_b32.
+// On return every wave has passed a barrier after its last LDS read.
+template <int RP, bool BKM>
+__device__ __forceinline__ void chain_project(const Operand& A, const Operand& B, int m0, int nk, char* lds,
+                                              f32x4 (&acc)[1][RP / 32]) {
+    using S = ChainShape<float, RP>;
+    constexpr int NST = S::NST, TA = kChainRows * kRowBytes, STAGE = (kChainRows + RP) * kRowBytes;
+    constexpr int PB = RP / 32, kLoads = 1 + PB;   // 1 KB instructions per wave and chunk
+    constexpr int SEG = RP / 4, KR = 64 / SEG;     // MN-major: 16-byte segments per k-row, k-rows per instruction
+    constexpr int SW = RP == 32 ? 1 : 3;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g = lane >> 4, wm0 = (wave >> 1) * 16, wn0 = (wave & 1) * (RP / 2);
+    const int64_t lda = A.s[0].ld, ldb = B.s[0].ld;
+    const int klen = A.s[0].klen;
+    auto load = [&](int i, int st) __attribute__((always_inline)) {   // chunk i, or nothing past the last
+        const bool live = i < nk;
+        const int k0 = 32 * i, rr = lane >> 3;
+        char* dst = lds + st * STAGE;
+        // K-major rows 8b .. 8b+7 at block b
+        auto rows = [&](const Operand& op, int64_t row0, int64_t ld, int b, char* to) {
+            const i32x4 d = make_desc(op.s[0].ptr + row0 * ld * 4, live ? (op.rows - row0) * ld * 4 : 0);
+            const int k = k0 + ((lane & 7) ^ rr ^ (b & 7)) * 4;
+            dma16(d, to + b * 1024, k < klen ? (uint32_t)((rr * ld + k) * 4) : kOOB, (uint32_t)(8 * b * ld * 4));
+        };
+        rows(A, m0, lda, wave, dst);
+#pragma unroll
+        for (int j = 0; j < PB; ++j) {
+            const int b = 4 * j + wave;
+            if constexpr (BKM) {
+                rows(B, 0, ldb, b, dst + TA);
+            } else {
+                const i32x4 d = make_desc(B.s[0].ptr + (live ? (int64_t)k0 * ldb * 4 : 0),
+                                          live ? (int64_t)(klen - k0) * ldb * 4 : 0);
+                const int k = KR * b + lane / SEG;
+                const int col = 4 * ((lane % SEG) ^ (4 * ((k >> 2) & SW)));
+                dma16(d, dst + TA + b * 1024, col < B.rows ? (uint32_t)(((lane / SEG) * ldb + col) * 4) : kOOB,
+                      (uint32_t)(KR * b * ldb * 4));
+            }
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < NST - 1; ++i) load(i, i);
+    int st = 0;
+    for (int i = 0; i < nk; ++i) {
+        wait_vmcnt<(NST - 2) * kLoads>();   // chunk i has landed
+        __syncthreads();                    // for every wave, and all are done with chunk i - 1
+        load(i + NST - 1, st == 0 ? NST - 1 : st - 1);
+        const char* ta = lds + st * STAGE;
+        const char* tb = ta + TA;
+        if constexpr (BKM) {
+            mma_chunk<float, 1, RP / 32>(ta, tb, wm0, wn0, lane, acc);
+        } else {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const u32x4 a = *reinterpret_cast<const u32x4*>(ta + lds_off(wm0 + r16, 4 * s + g));
+#pragma unroll
+                for (int j = 0; j < RP / 32; ++j) {
+                    const char* p = tb + (16 * s + 4 * g) * 4 * RP + ((wn0 + 16 * j + r16) ^ (16 * (g & SW))) * 4;
+                    u32x4 b;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) b[e] = *reinterpret_cast<const uint32_t*>(p + 4 * RP * e);
+                    mma<float>(acc[0][j], a, b);
+                }
+            }
+        }
+        st = st + 1 == NST ? 0 : st + 1;
+    }
+    wait_vmcnt<0>();   // the caller reuses the stages
+    __syncthreads();
+}
 
 // Element (row, col) of a kChainRows x RP operand tile laid out as NKB K chunks.
 template <typename E>
@@ -282,7 +363,7 @@ template <typename E, int RP, Act F, int L>
 __global__ __launch_bounds__(kThreads) void fwd_chain_kernel(ChainArgs a) {
     using S = ChainShape<E, RP>;
     constexpr int TN = S::TN;
-    __shared__ __attribute__((aligned(16))) char lds[S::LDS];
+    __shared__ __attribute__((aligned(1024))) char lds[S::LDS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, g = lane >> 4;
     const int wm0 = (wave >> 1) * 16, wn0 = (wave & 1) * (RP / 2);
@@ -294,7 +375,7 @@ __global__ __launch_bounds__(kThreads) void fwd_chain_kernel(ChainArgs a) {
     f32x4 acc[1][TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[0][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    mainloop<E, kChainRows, RP, 2, 2, true, false>(a.A, a.B, m0, 0, 0, a.nk, lds, acc);
+    chain_project<RP, false>(a.A, a.B, m0, a.nk, lds, acc);
 
     char* Cb = lds;
     char* Mb = lds + S::NKB * kChainRows * kRowBytes;
@@ -379,7 +460,7 @@ template <typename E, int RP, Act F, int L>
 __global__ __launch_bounds__(kThreads) void bwd_chain_kernel(ChainArgs a) {
     using S = ChainShape<E, RP>;
     constexpr int TN = S::TN;
-    __shared__ __attribute__((aligned(16))) char lds[S::LDS];
+    __shared__ __attribute__((aligned(1024))) char lds[S::LDS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, g = lane >> 4;
     const int wm0 = (wave >> 1) * 16, wn0 = (wave & 1) * (RP / 2);
@@ -392,7 +473,7 @@ __global__ __launch_bounds__(kThreads) void bwd_chain_kernel(ChainArgs a) {
     f32x4 dc2[1][TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) dc2[0][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    mainloop<E, kChainRows, RP, 2, 2, true, true>(a.A, a.B, m0, 0, 0, a.nk, lds, dc2);
+    chain_project<RP, true>(a.A, a.B, m0, a.nk, lds, dc2);
 
     char* Cb = lds;
     char* Mb = lds + S::NKB * kChainRows * kRowBytes;

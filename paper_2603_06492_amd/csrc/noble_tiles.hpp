@@ -251,42 +251,4 @@ __device__ __forceinline__ void mma_chunk(const char* ldsA, const char* ldsB, in
     }
 }
 
-// Double-buffered main loop over K chunks [kc0, kc1) of a BM x BN tile whose
-// top-left output is (m0, n0).  Four waves as WM x WN.  `lds` must hold
-// 2 * (BM + BN) * 128 bytes.  On return every wave has passed a barrier after
-// its last LDS read, so the caller may reuse `lds`.
-template <typename E, int BM, int BN, int WM, int WN, bool AK, bool BKM>
-__device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int m0, int n0,
-                                         int kc0, int kc1, char* lds,
-                                         f32x4 (&acc)[BM / WM / 16][BN / WN / 16]) {
-    static_assert(WM * WN == 4, "four waves");
-    constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
-    constexpr int STAGE = (BM + BN) * kRowBytes;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
-    if (kc0 >= kc1) return;
-    Stage<E, BM, AK> sa;
-    Stage<E, BN, BKM> sb;
-    sa.load(A, m0, kc0, tid);
-    sb.load(B, n0, kc0, tid);
-    sa.store(lds, tid);
-    sb.store(lds + BM * kRowBytes, tid);
-    __syncthreads();
-    for (int kc = kc0; kc < kc1; ++kc) {
-        char* cur = lds + ((kc - kc0) & 1) * STAGE;
-        char* nxt = lds + (((kc - kc0) & 1) ^ 1) * STAGE;
-        const bool more = kc + 1 < kc1;
-        if (more) {
-            sa.load(A, m0, kc + 1, tid);
-            sb.load(B, n0, kc + 1, tid);
-        }
-        mma_chunk<E, TM, TN>(cur, cur + BM * kRowBytes, wm0, wn0, lane, acc);
-        if (more) {
-            sa.store(nxt, tid);
-            sb.store(nxt + BM * kRowBytes, tid);
-        }
-        __syncthreads();
-    }
-}
-
 }  // namespace noble
