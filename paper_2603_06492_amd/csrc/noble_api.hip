@@ -413,6 +413,38 @@ size_t fwd_split_need(const noble_linear_desc* d) {
     return w.split > 0 ? split_need(d, w.split) : 0;
 }
 
+// y or dx as one launch of tile t1 (rows1 = M), or as its full waves of
+// tile t1 over the first rows1 rows and a second launch of tile t2 over the
+// rest.  A launch a little over a number of waves spends a whole wave on the
+// few tiles left; smaller tiles finish those rows sooner (kLaunchUs for the
+// second launch, taken when the model gains 6%).  Training step, one launch /
+// two (us): 9000 x 2048 -> 2048 369 / 336, 10000 x 2048 -> 8192 1108 / 1066,
+// 25216 x 3072 -> 768 505 / 489; at a model gain of 3 to 6%, 5000 x 2048 ->
+// 3 x 2048 479 / 484.
+struct DensePlan {
+    TileId t1;
+    int64_t rows1;
+    TileId t2;
+};
+DensePlan plan_dense(int64_t G, int64_t M, int64_t N, int nk) {
+    constexpr double kLaunchUs = 4.0, kGain = 0.94;
+    DensePlan p{pick_tile(G, M, N, nk), M, kTile256};
+    double best = kGain * tile_cost(p.t1, G, M, N, nk);
+    for (int i = 0; i < kTile32x128; ++i) {
+        const TileCost& t = kTileCost[i];
+        const int64_t per_row = G * ((N + t.bn - 1) / t.bn), blocks = (M + t.bm - 1) / t.bm * per_row;
+        const int64_t rows1 = blocks / t.slots * t.slots / per_row * t.bm;   // row blocks of the full waves
+        if (rows1 <= 0 || rows1 >= M) continue;
+        const TileId t2 = pick_tile(G, M - rows1, N, nk);
+        const double c = tile_cost((TileId)i, G, rows1, N, nk) + tile_cost(t2, G, M - rows1, N, nk) + kLaunchUs;
+        if (c < best) {
+            best = c;
+            p = DensePlan{(TileId)i, rows1, t2};
+        }
+    }
+    return p;
+}
+
 // Output tile of a float32 launch that has b128 workgroups of 128 x 128 tiles
 // or b64 of 64 x 64.  The float32 MFMAs are slow enough (a 128 x 128 tile's
 // 32-element chunk takes 1.7 us) that a launch of less than a wave of 128 x
@@ -699,20 +731,28 @@ noble_status launch_dense(const Batch<DenseBatch>& bt, TileId tile, hipStream_t 
     }
 }
 
-// Empty batch for y or dx, G problems [M, N] of nk chunks each.
-template <typename E>
-Batch<DenseBatch> dense_batch(int64_t G, int64_t M, int64_t N, int nk, TileId& tile) {
-    Batch<DenseBatch> bt;
-    tile = kTile256;
+// y or dx, G problems [M, N] of nk chunks each: `add(batch, row, rows)` adds
+// the problems of `rows` rows from `row`.
+template <typename E, bool BKM, typename Add>
+noble_status run_dense(int64_t G, int64_t M, int64_t N, int nk, hipStream_t st, bool plain, Add add) {
     if constexpr (sizeof(E) == 2) {
-        tile = pick_tile(G, M, N, nk);
-        bt.bm = kTileCost[tile].bm;
-        bt.bn = kTileCost[tile].bn;
+        const DensePlan p = plan_dense(G, M, N, nk);
+        auto run = [&](TileId tile, int64_t row, int64_t rows) {
+            Batch<DenseBatch> bt;
+            bt.bm = kTileCost[tile].bm;
+            bt.bn = kTileCost[tile].bn;
+            add(bt, row, rows);
+            return launch_dense<E, BKM>(bt, tile, st, plain);
+        };
+        NOBLE_TRY(run(p.t1, 0, p.rows1));
+        return p.rows1 < M ? run(p.t2, p.rows1, M - p.rows1) : NOBLE_OK;
     } else {
+        Batch<DenseBatch> bt;
         auto blocks = [&](int64_t t) { return G * ((M + t - 1) / t) * ((N + t - 1) / t); };
         bt.bm = bt.bn = f32_tile(blocks(128), blocks(64));
+        add(bt, 0, M);
+        return launch_dense<E, BKM>(bt, kTile256, st, plain);
     }
-    return bt;
 }
 
 // float32 path: chain kernels with their own rank projection, one launch per
@@ -973,17 +1013,19 @@ noble_status fwd_impl(const noble_linear_desc* d, const void* x, const void* W, 
     constexpr int GBK = gemm_bk<E>();
     const int nk1 = cdiv(din, GBK);
     const int nk = nk1 + (r > 0 ? cdiv(r, GBK) : 0);
-    TileId tile;
-    Batch<DenseBatch> bt = dense_batch<E>(G, T, dog, nk, tile);
-    for (int g = 0; g < G; ++g) {
-        const E* Wg = static_cast<const E*>(W) + g * dog;
-        const char* C2g = C2s + g * r * (int64_t)ES;
-        const E* Wug = r > 0 ? static_cast<const E*>(Wu) + g * r * dog : nullptr;
-        bt.add(operand2(seg(x, din, din), seg(C2g, R, r), nk1, T), operand2(seg(Wg, dout, din), seg(Wug, dog, r), nk1, dog),
-               (int)T, (int)dog, nk, static_cast<E*>(y) + g * dog, dout, sizeof(E) == 4, b ? b + g * dog : nullptr,
-               nullptr, 1);
-    }
-    return launch_dense<E, false>(bt, tile, st, r == 0 && G == 1);
+    auto add = [&](Batch<DenseBatch>& bt, int64_t m0, int64_t rows) {
+        const E* xm = static_cast<const E*>(x) + m0 * din;
+        for (int g = 0; g < G; ++g) {
+            const E* Wg = static_cast<const E*>(W) + g * dog;
+            const char* C2g = C2s + (m0 * R + g * r) * (int64_t)ES;
+            const E* Wug = r > 0 ? static_cast<const E*>(Wu) + g * r * dog : nullptr;
+            bt.add(operand2(seg(xm, din, din), seg(C2g, R, r), nk1, rows),
+                   operand2(seg(Wg, dout, din), seg(Wug, dog, r), nk1, dog), (int)rows, (int)dog, nk,
+                   static_cast<E*>(y) + m0 * dout + g * dog, dout, sizeof(E) == 4, b ? b + g * dog : nullptr, nullptr,
+                   1);
+        }
+    };
+    return run_dense<E, false>(G, T, dog, nk, st, r == 0 && G == 1, add);
 }
 
 template <typename E>
@@ -1107,11 +1149,13 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
     {
         const int nk1 = cdiv(dout, GBK);
         const int nk = nk1 + (r > 0 ? cdiv(R, GBK) : 0);
-        TileId tile;
-        Batch<DenseBatch> bt = dense_batch<E>(1, T, din, nk, tile);
-        bt.add(operand2(seg(dy, dout, dout), seg(dHs, hl * R, R), nk1, T), operand2(seg(W, dout, dout), seg(Wd, R, R), nk1, din),
-               (int)T, (int)din, nk, dx, din, sizeof(E) == 4, nullptr, nullptr, 1);
-        NOBLE_TRY((launch_dense<E, true>(bt, tile, st)));
+        auto add = [&](Batch<DenseBatch>& bt, int64_t m0, int64_t rows) {
+            bt.add(operand2(seg(static_cast<const E*>(dy) + m0 * dout, dout, dout),
+                            seg(dHs + m0 * hl * R * (int64_t)ES, hl * R, R), nk1, rows),
+                   operand2(seg(W, dout, dout), seg(Wd, R, R), nk1, din), (int)rows, (int)din, nk,
+                   static_cast<E*>(dx) + m0 * din, din, sizeof(E) == 4, nullptr, nullptr, 1);
+        };
+        NOBLE_TRY((run_dense<E, true>(1, T, din, nk, st, false, add)));
     }
 
     // Weight gradients, reduced over tokens (K = T), A and B both MN-major, in

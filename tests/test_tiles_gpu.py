@@ -22,6 +22,10 @@ CASES = [
     ("128_T1990", 1990, 2040, 2040, 40, 1),
     ("256x128_T8190", 8190, 1016, 1016, 40, 1),
     ("256_T8190", 8190, 2040, 2040, 72, 1),
+    # y: the full wave as 256 x 256 tiles (8192 rows), then the last 258 rows
+    ("256_then_64x128_T8450", 8450, 1016, 2040, 40, 1),
+    # dx alike; y in three groups
+    ("two_launches_T8450_g3", 8450, 2040, 3 * 680, 24, 3),
 ]
 
 
