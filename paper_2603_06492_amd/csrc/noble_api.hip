@@ -1257,10 +1257,11 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
             }
         }
         if (red.count > 0) {
-            // up to 1024 blocks of 256 threads per array, four floats per thread
+            // up to 4096 blocks of 256 threads per array, four floats per thread: a
+            // thread that loops waits for each iteration's slices
             red.first[0] = 0;
             for (int a = 0; a < red.count; ++a)
-                red.first[a + 1] = red.first[a] + (int)std::min<int64_t>(1024, std::max<int64_t>(1, cdiv(red.n[a], 4 * 256)));
+                red.first[a + 1] = red.first[a] + (int)std::min<int64_t>(4096, std::max<int64_t>(1, cdiv(red.n[a], 4 * 256)));
             NOBLE_TRY(launch(reduce_kernel, dim3(red.first[red.count]), dim3(256), st, red));
         }
     }
