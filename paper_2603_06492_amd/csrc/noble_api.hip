@@ -803,7 +803,9 @@ noble_status launch_proj(bool fwd, const noble_linear_desc* d, const void* A, co
     a.nk = cdiv(fwd ? din : dog, 64);
     a.S = S;
     const dim3 grid = flat_grid((int64_t)cdiv(T, kPjRows) * S * a.J), block(kPjThreads);
-    return fwd ? launch(proj_kernel<false>, grid, block, st, a) : launch(proj_kernel<true>, grid, block, st, a);
+    if (r <= 64)
+        return fwd ? launch(proj_kernel<false, 64>, grid, block, st, a) : launch(proj_kernel<true, 64>, grid, block, st, a);
+    return fwd ? launch(proj_kernel<false, 128>, grid, block, st, a) : launch(proj_kernel<true, 128>, grid, block, st, a);
 }
 
 // bf16 path, step 2: the branch nonlinearity (forward or backward) from the

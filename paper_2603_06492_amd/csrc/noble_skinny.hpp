@@ -2,7 +2,7 @@
 //
 //   proj_kernel:        the rank projection, H = x W_down (forward) or
 //                       dC2 = dy W_up^T (backward), as a split-K MFMA product:
-//                       a workgroup owns 128 tokens x all 128 (padded) ranks
+//                       a workgroup owns 128 tokens x all 128 (padded; 64 at r <= 64) ranks
 //                       and one of S pieces of K, and writes its float32
 //                       partial sum to scratch.  Streaming 128 tokens against
 //                       the rank operand (instead of 32) cuts the L2 traffic of
@@ -37,7 +37,7 @@
 // workgroup per (token block, group).
 #pragma once
 
-#include "noble_gemm_dma.hpp"
+#include "noble_gemm_tile.hpp"
 #include "noble_kernels.hpp"
 
 namespace noble {
@@ -91,11 +91,19 @@ __device__ __forceinline__ BfTriple bf_split3(float v) {
 
 constexpr int kPjRows = 128;                 // tokens per projection workgroup
 constexpr int kPjThreads = 512;              // eight waves: 4 token blocks x 2 rank halves
-constexpr int kPjStages = 4;                 // LDS ring depth
 constexpr int kPjA = kPjRows * 128;          // A bytes per stage (128 rows x 64 K)
-constexpr int kPjB = kSkN * 128;             // B bytes per stage (16 KB either layout)
-constexpr int kPjStage = kPjA + kPjB;
-constexpr int kPjLoads = 4;                  // DMA instructions per wave per K chunk
+// Shape by the job's padded rank columns BN (128, or 64 for r <= 64): bytes of
+// a stage, ring depth, DMA instructions per wave per K chunk.  At BN = 64 the
+// ring takes 72 KB, so two workgroups share a CU: while one waits at its
+// barrier for its chunk, the other's loads are in flight; and W_down's tile
+// no longer carries 64 columns of zeros.  Training steps with 128 columns and
+// with 64 (us): 25216 x 3072 -> 768, r = 32, 471 / 463; 25216 x 768 -> 3072
+// 498 / 487; 4096 x 2048 -> 3 x 2048, r = 64, 370 / 361; 8192 x 1024 -> 3072,
+// r = 64, 230 / 229.
+template <int BN>
+struct PjShape {
+    static constexpr int STAGE = kPjA + BN * 128, NST = BN == 128 ? 4 : 3, LOADS = 2 + BN / 64;
+};
 constexpr int kPjMinChunks = 4;              // 64-element K chunks per piece, at least
 constexpr int kPjMaxSplit = 8;
 constexpr int kPjMaxJobs = 8;                // (group, 128-rank block) pairs per launch
@@ -159,9 +167,9 @@ struct BranchArgs {
 constexpr int kChainCopies = 8;
 
 
-// One 64-element K chunk of the projection operands: 4 DMA instructions per
-// wave (two for A, two for B).
-template <bool BKM>
+// One 64-element K chunk of the projection operands: two DMA instructions per
+// wave for A, BN / 64 for B.
+template <bool BKM, int BN>
 __device__ __forceinline__ void proj_dma(const Operand& A, const Operand& B, int row0, int kc, char* st, int wave,
                                          int lane) {
     constexpr int ES = 2;
@@ -170,22 +178,32 @@ __device__ __forceinline__ void proj_dma(const Operand& A, const Operand& B, int
     // c ^ swz(q), swz(q) = (q ^ q/8) & 7, so a 16-row pass of ds_read_b128
     // covers all banks.  128 rows x 128 B: block b = 8i + w holds rows
     // 8b .. 8b+7; lane p -> row 8b + p/8, and swz = (p/8) ^ w.
-    auto kmajor = [&](const Operand& op, int64_t row_base, char* dst) {
+    auto kmajor = [&](const Operand& op, int64_t row_base, char* dst, int per) {
         const int64_t ld = op.s[0].ld;
         const i32x4 rs = make_desc(op.s[0].ptr + row_base * ld * ES, (int64_t)(op.rows - row_base) * ld * ES);
         const int rr = lane >> 3, c = (lane & 7) ^ rr ^ wave;
         const int k = k0 + c * 8;
         const uint32_t vo = k < op.s[0].klen ? (uint32_t)(((int64_t)rr * ld + k) * ES) : kOOB;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < per; ++i) {
             const int b = 8 * i + wave;
             dma16(rs, dst + b * 1024, vo, (uint32_t)((int64_t)8 * b * ld * ES));
         }
     };
-    kmajor(A, row0, st);
+    kmajor(A, row0, st, 2);
     char* dst = st + kPjA;
     if constexpr (BKM) {
-        kmajor(B, 0, dst);
+        kmajor(B, 0, dst, BN / 64);
+    } else if constexpr (BN == 64) {
+        // 64 k-rows x 128 B in TileFrag's layout: block w holds k-rows 8w .. 8w+7;
+        // lane p -> k-row 8w + p/8, physical segment p%8 holding logical
+        // (p%8) ^ 4((k / 2) & 1)
+        const int64_t ld = B.s[0].ld;
+        const int klen = B.s[0].klen, kq = lane >> 3;
+        const i32x4 rs = make_desc(B.s[0].ptr + (int64_t)k0 * ld * ES, (int64_t)(klen - k0) * ld * ES);
+        const int col = 8 * ((lane & 7) ^ (4 * ((kq >> 1) & 1)));
+        dma16(rs, dst + wave * 1024, col < B.rows ? (uint32_t)(((int64_t)kq * ld + col) * ES) : kOOB,
+              (uint32_t)((int64_t)8 * wave * ld * ES));
     } else {
         // 64 k-rows x 256 B, block b = 8i + w holds k-rows 4b .. 4b+3; lane p ->
         // k-row 4b + p/16, physical segment p%16 holding logical (p%16) ^ 4(p/16)
@@ -321,10 +339,12 @@ __device__ __forceinline__ void mix_mma1(const char* c, const char* mt, int wave
 
 // Split-K rank projection.  Workgroup g: token block g % blocks, K piece
 // (g / blocks) % S, job g / (blocks S).  Wave w owns rows 32 (w / 2) .. +31
-// and rank columns 64 (w % 2) .. +63 of the job's 128 x 128 tile (two
-// 32x32x16 MFMAs per K step).
-template <bool BKM>
-__global__ __launch_bounds__(kPjThreads, 1) void proj_kernel(ProjArgs a) {
+// and BN / 2 rank columns from BN / 2 (w % 2) of the job's 128 x BN tile
+// (BN / 64 32x32x16 MFMAs per K step).
+template <bool BKM, int BN>
+__global__ __launch_bounds__(kPjThreads, BN == 64 ? 4 : 1) void proj_kernel(ProjArgs a) {
+    using S = PjShape<BN>;
+    constexpr int kPjStages = S::NST, kPjStage = S::STAGE, kPjLoads = S::LOADS, NJ = BN / 64;
     __shared__ __attribute__((aligned(1024))) char lds[kPjStages * kPjStage];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, h = lane >> 5;
@@ -341,24 +361,27 @@ __global__ __launch_bounds__(kPjThreads, 1) void proj_kernel(ProjArgs a) {
 
     // A rows 32 wr + r32: swz = (r32 & 7) ^ (r32 >> 3) ^ 4(wr & 1)
     const uint32_t fa = (uint32_t)((32 * wr + r32) * 128 + ((h ^ (r32 & 7) ^ (r32 >> 3) ^ (4 * (wr & 1))) << 4));
-    uint32_t fb[2];
+    uint32_t fb[NJ];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        if constexpr (BKM)   // W_up rows 64 wc + 32 j + r32: swz = (r32 & 7) ^ (r32 >> 3) ^ 4(j & 1)
-            fb[j] = (uint32_t)((64 * wc + 32 * j + r32) * 128 + ((h ^ (r32 & 7) ^ (r32 >> 3) ^ (4 * (j & 1))) << 4));
+    for (int j = 0; j < NJ; ++j) {
+        // W_up rows BN/2 wc + 32 j + r32: swz = (r32 & 7) ^ (r32 >> 3) ^ 4 (32-row block & 1)
+        const int blk = NJ * wc + j;
+        if constexpr (BKM)
+            fb[j] = (uint32_t)((32 * blk + r32) * 128 + ((h ^ (r32 & 7) ^ (r32 >> 3) ^ (4 * (blk & 1))) << 4));
         else
-            fb[j] = tr_base(2 * wc + j, lane);
+            fb[j] = tr_base(blk, lane);   // BN = 128
     }
-    f32x16 acc[2];
+    const TileFrag<false, 64, 1> fb64(32 * wc, lane);   // BN = 64, MN-major
+    f32x16 acc[NJ];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
 
     const int n = kc1 - kc0;
 #pragma unroll
     for (int c = 0; c < kPjStages - 1; ++c)
-        if (c < n) proj_dma<BKM>(jb.A, jb.B, row0, kc0 + c, lds + c * kPjStage, wave, lane);
+        if (c < n) proj_dma<BKM, BN>(jb.A, jb.B, row0, kc0 + c, lds + c * kPjStage, wave, lane);
 
     // The zeroing rides on the projection: every workgroup clears a strided
     // share while its first loads are in flight.
@@ -377,7 +400,7 @@ __global__ __launch_bounds__(kPjThreads, 1) void proj_kernel(ProjArgs a) {
     for (int i = 0; i < n; ++i) {
         // chunk i has landed once at most (stages - 2) later chunks are in flight
         const int ahead = min(n - 1 - i, kPjStages - 2);
-        if (ahead >= 2)
+        if (kPjStages > 3 && ahead >= 2)
             wait_vmcnt<2 * kPjLoads>();
         else if (ahead == 1)
             wait_vmcnt<kPjLoads>();
@@ -385,7 +408,7 @@ __global__ __launch_bounds__(kPjThreads, 1) void proj_kernel(ProjArgs a) {
             wait_vmcnt<0>();
         __syncthreads();
         if (i + kPjStages - 1 < n)
-            proj_dma<BKM>(jb.A, jb.B, row0, kc0 + i + kPjStages - 1,
+            proj_dma<BKM, BN>(jb.A, jb.B, row0, kc0 + i + kPjStages - 1,
                           lds + ((i + kPjStages - 1) % kPjStages) * kPjStage, wave, lane);
         const char* st = lds + (i % kPjStages) * kPjStage;
         const char* sb = st + kPjA;
@@ -393,10 +416,12 @@ __global__ __launch_bounds__(kPjThreads, 1) void proj_kernel(ProjArgs a) {
         for (int s = 0; s < 4; ++s) {
             const u32x4 av = *reinterpret_cast<const u32x4*>(st + (fa ^ ((uint32_t)s << 5)));
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < NJ; ++j) {
                 u32x4 bv;
                 if constexpr (BKM)
                     bv = *reinterpret_cast<const u32x4*>(sb + (fb[j] ^ ((uint32_t)s << 5)));
+                else if constexpr (BN == 64)
+                    bv = fb64.read(sb, 0, s);
                 else
                     bv = tr_read8(sb, fb[j], s);
                 mma32<uint16_t>(acc[j], av, bv);
@@ -404,7 +429,7 @@ __global__ __launch_bounds__(kPjThreads, 1) void proj_kernel(ProjArgs a) {
         }
     }
 
-    // acc[j][v]: row 32 wr + 8(v/4) + 4h + v%4, column c0 + 64 wc + 32 j + r32;
+    // acc[j][v]: row 32 wr + 8(v/4) + 4h + v%4, column c0 + BN/2 wc + 32 j + r32;
     // rows past T are dropped by the buffer range check, columns past the
     // job's width by the kOOB offset
     const int ldp = a.ldp, n_cols = jb.B.rows;
@@ -412,8 +437,8 @@ __global__ __launch_bounds__(kPjThreads, 1) void proj_kernel(ProjArgs a) {
         make_rsrc(reinterpret_cast<const char*>(a.P + piece * a.pstride + jb.c0) + (int64_t)row0 * ldp * 4,
                   (int64_t)(a.T - row0) * ldp * 4);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int col = 64 * wc + 32 * j + r32;
+    for (int j = 0; j < NJ; ++j) {
+        const int col = 32 * (NJ * wc + j) + r32;
         const uint32_t vo = col < n_cols ? (uint32_t)(((32 * wr + 4 * h) * ldp + col) * 4) : kOOB;
 #pragma unroll
         for (int v = 0; v < 16; ++v)
