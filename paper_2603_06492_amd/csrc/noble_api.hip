@@ -451,9 +451,10 @@ DensePlan plan_dense(int64_t G, int64_t M, int64_t N, int nk) {
 // 128 tiles is bound by its longest CU; a 64 x 64 tile takes 0.28 of the time
 // of a 128 x 128 one when both fill the chip, and several share a CU.
 // Forward / backward, 128 against 64 (us): 2048 x 768 -> 768 83 / 130 and
-// 60 / 101, 256 x 64 -> 64 16 / 42 and 11 / 24, 4096 x 256 -> 256 34 / 67 and
-// 22 / 47; at a full wave, 4096 x 1024 -> 1024, 116 / 233 and 117 / 234, and
-// beyond, 8192 x 2048 -> 2048, 638 / 1333 and 711 / 1415.
+// 52 / 93, 256 x 64 -> 64 16 / 42 and 11 / 24, 4096 x 256 -> 256 34 / 67 and
+// 19 / 45; with 64 x 64 tiles staged through registers, at a full wave, 4096 x
+// 1024 -> 1024, 116 / 233 and 117 / 234, and beyond, 8192 x 2048 -> 2048, 638 /
+// 1333 and 711 / 1415.
 int f32_tile(int64_t b128, int64_t b64) {
     return 0.28 * (double)((b64 + 255) / 256) < (double)((b128 + 255) / 256) ? 64 : 128;
 }
