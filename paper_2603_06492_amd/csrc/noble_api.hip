@@ -288,8 +288,9 @@ int gemm_tile_of(const noble_linear_desc* d) {
 
 // Largest workgroup count of one GEMM launch: a dispatch counts its
 // work-items in 32 bits.
+constexpr int64_t max_blocks(int threads) { return (int64_t)UINT32_MAX / threads; }
 int64_t max_gemm_blocks(const noble_linear_desc* d) {
-    return (int64_t)UINT32_MAX / (d->dtype == NOBLE_BF16 ? kDmaThreads : kThreads);
+    return max_blocks(d->dtype == NOBLE_BF16 ? kDmaThreads : kThreads);
 }
 
 // bf16 products (256-square tiles) of at most 128 rows without column sums
@@ -454,8 +455,11 @@ DensePlan plan_dense(int64_t G, int64_t M, int64_t N, int nk) {
 // 52 / 93, 256 x 64 -> 64 16 / 42 and 11 / 24, 4096 x 256 -> 256 34 / 67 and
 // 19 / 45; with 64 x 64 tiles staged through registers, at a full wave, 4096 x
 // 1024 -> 1024, 116 / 233 and 117 / 234, and beyond, 8192 x 2048 -> 2048, 638 /
-// 1333 and 711 / 1415.
+// 1333 and 711 / 1415.  A launch of at most 64 columns has only twice the
+// workgroups on 64 x 64 tiles and takes them at any length, up to the dispatch
+// limit, which check_grids applies to the 128 x 128 tiles.
 int f32_tile(int64_t b128, int64_t b64) {
+    if (b64 > max_blocks(kThreads)) return 128;
     return 0.28 * (double)((b64 + 255) / 256) < (double)((b128 + 255) / 256) ? 64 : 128;
 }
 
