@@ -436,6 +436,7 @@ DensePlan plan_dense(int64_t G, int64_t M, int64_t N, int nk) {
         const int64_t per_row = G * ((N + t.bn - 1) / t.bn), blocks = (M + t.bm - 1) / t.bm * per_row;
         const int64_t rows1 = blocks / t.slots * t.slots / per_row * t.bm;   // row blocks of the full waves
         if (rows1 <= 0 || rows1 >= M) continue;
+        if (rows1 / t.bm * per_row > max_blocks(kDmaThreads)) continue;   // past one dispatch of 512 threads each
         const TileId t2 = pick_tile(G, M - rows1, N, nk);
         const double c = tile_cost((TileId)i, G, rows1, N, nk) + tile_cost(t2, G, M - rows1, N, nk) + kLaunchUs;
         if (c < best) {

@@ -3,7 +3,7 @@ tests/c/launch_record.cpp (HIP's launch function replaced, no GPU): what the
 launch rules choose, and that every launch can be made."""
 
 import os
-import re
+import random
 import shutil
 import subprocess
 
@@ -73,3 +73,37 @@ def test_float32_launches_stay_within_a_dispatch(record, T, di, do, r):
     for st, launches, _ in record(calls):
         assert st == 0 and launches
         assert not _oversize(launches)
+
+
+# bf16, 384 columns: three 256 x 128 tiles per row block against two 256 x 256 ones
+BF16_LONG = [(720000000, 8, 384), (720000000, 384, 8), ((1 << 31) - 4096, 8, 128), ((1 << 30) - 256, 8, 384)]
+
+
+@pytest.mark.parametrize("T,di,do", BF16_LONG)
+@pytest.mark.parametrize("r", [0, 8])
+def test_bf16_launches_stay_within_a_dispatch(record, T, di, do, r):
+    """The full waves of a two-launch product are of tiles that fit a dispatch, like the single launch."""
+    for st, launches, _ in record([(c, T, di, do, r, "bf16", "cosnet", 1) for c in ("fwd", "bwd")]):
+        assert st == 0 and launches
+        assert not _oversize(launches)
+
+
+def test_every_accepted_call_can_be_launched(record):
+    """Shapes spread over the ABI's ranges: a call is refused before any launch, or all of its launches fit."""
+    rng = random.Random(1)
+    calls = []
+    for _ in range(1500):
+        G = rng.choice((1, 1, 2, 3, 4))
+        T = min(int(2 ** rng.uniform(0, 31)), 2 ** 31 - 4096)
+        di, do = (8 * max(1, int(2 ** rng.uniform(0, 17))) for _ in range(2))
+        do = max(1, do // (8 * G)) * 8 * G
+        dt = rng.choice(("bf16", "f32"))
+        r = rng.choice((0, 8, 40, 128, 256 if dt == "bf16" else 96))
+        act = rng.choice(("cosnet", "gelu", "cosnet3" if r <= 128 else "tanh_m"))
+        calls += [(c, T, di, do, r, dt, act, G) for c in ("fwd", "bwd")]
+    taken = 0
+    for call, (st, launches, _) in zip(calls, record(calls)):
+        assert not _oversize(launches), call
+        assert st == 0 or not launches, call
+        taken += st == 0
+    assert taken > 2000
