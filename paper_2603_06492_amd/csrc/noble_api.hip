@@ -1090,7 +1090,7 @@ noble_status bwd_impl(const noble_linear_desc* d, const void* dy, const void* x,
             zero(dWd, din * R);
             zero(dWu, R * dog);
         }
-        if (T == 0 || !two) zero(dM, nm * G * r * r);
+        if (T == 0 || !two) zero(dM, nm * G * r * r / (lowp ? 2 : 1));   // counted in floats
         if (copies && T > 0) {
             // the reduction of the copies overwrites dw1, dp1 (and dw2, dp2)
             zero(copies, (int64_t)nvec(d) * kChainCopies * R);

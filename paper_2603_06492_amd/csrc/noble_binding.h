@@ -11,7 +11,8 @@ extern "C" {
 
 /* noble_linear_bwd with the gradients of the storage parameters (dW, dW_down,
  * dM, dW_up) in the storage dtype: the float32 sums of noble_linear_bwd rounded
- * once.  T = 0 is refused on the bf16 path (NOBLE_ERR_BAD_SHAPE). */
+ * once.  With a one-application activation a given dM, in the storage dtype too,
+ * is set to zero.  T = 0 is refused on the bf16 path (NOBLE_ERR_BAD_SHAPE). */
 noble_status noble_linear_bwd_storage(const noble_linear_desc* desc, const void* dy, const void* x, const void* W,
                                       const void* W_down, const float* omega1, const float* phi1, const void* M,
                                       const float* omega2, const float* phi2, const void* W_up, const void* reserve,

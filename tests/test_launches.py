@@ -107,3 +107,16 @@ def test_every_accepted_call_can_be_launched(record):
         assert st == 0 or not launches, call
         taken += st == 0
     assert taken > 2000
+
+
+@pytest.mark.parametrize("act", ["cos", "gelu", "tanh", "leaky_relu"])
+@pytest.mark.parametrize("G,r", [(1, 8), (1, 40), (3, 24), (1, 256)])
+def test_unused_gradients_are_cleared_in_their_own_size(record, act, G, r):
+    """One application: the given dM, domega2 and dphi2 are set to zero, dM in float32 (the public backward) or in the
+    storage dtype (the binding's)."""
+    size = {("bwd", "bf16"): 4, ("storage", "bf16"): 2, ("bwd", "f32"): 4, ("storage", "f32"): 4}
+    calls = [(c, 300, 64, 8 * G, r, dt, act, G) for c, dt in size if dt == "bf16" or r <= 128]
+    for call, (st, launches, zeros) in zip(calls, record(calls)):
+        assert st == 0 and launches
+        assert zeros["dM"] == G * r * r * size[call[0], call[5]], call
+        assert zeros["domega2"] == zeros["dphi2"] == G * r * 4, call
