@@ -109,7 +109,8 @@ struct Call {
         }
         act = (int)PyLong_AsLong(a);
         layers = (int)PyLong_AsLong(l);
-        G = PyLong_AsLong(g);
+        int wide = 0;   // past a long: G is -1, which is refused below
+        G = PyLong_AsLongAndOverflow(g, &wide);
         const at::Tensor *tx = tensor(x), *tw = tensor(W), *td = Wd == Py_None ? nullptr : tensor(Wd);
         if (!ok || tx->dim() != 2 || tw->dim() != 2 || (td && td->dim() != 2) || G < 1 || G > INT32_MAX) {
             ok = false;

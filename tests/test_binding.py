@@ -24,6 +24,21 @@ def test_native_leaves_other_calls_to_python():
         noble.noble_linear_fwd(x, W, None, *none, x, None, None)
 
 
+@pytest.mark.parametrize("groups", [2 ** 63, 2 ** 70, -2 ** 70, -1, 0, 2 ** 40])
+def test_native_leaves_groups_out_of_range_to_python(groups):
+    """Past a C long too: no error of the native code's own."""
+    torch = pytest.importorskip("torch")
+    n = noble._native()
+    x, W = torch.zeros(4, 64), torch.zeros(64, 64)
+    none = (None,) * 7
+    assert n.forward(False, 0, 2, groups, x, W, None, *none, x, None, None) is None
+    assert n.backward(0, 2, groups, x, x, W, *none, None, x, W, None, *none, None) is None
+    assert n.module_forward(True, 0, 2, groups, x, W, None, *none) is None
+    assert n.module_backward(False, 0, 2, groups, x, x, W, *none, None) is None
+    with pytest.raises(ZeroDivisionError if groups == 0 else ValueError):
+        noble.noble_linear_fwd(x, W, None, *none, x, None, None, groups=groups)
+
+
 # 1250 rows per batch entry: dW and the rank products split over K, so that the
 # reduction stores their gradients; 37: the products themselves store dW and dW_up
 CASES = [("cosnet", 1, 40, "bf16", 37), ("cosnet", 3, 16, "bf16", 37), ("gelu", 1, 40, "bf16", 37),
