@@ -220,7 +220,8 @@ PyObject* module_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (n != 14) Py_RETURN_NONE;
     const bool keep = a[0] == Py_True;
     Call c(a[1], a[2], a[3], a[4], a[5], a[7]);
-    if (!c.ok) Py_RETURN_NONE;
+    // A recorded plain layer has a W_down of no columns (the backward needs it); None is an error.
+    if (!c.ok || (keep && a[7] == Py_None)) Py_RETURN_NONE;
     const void* x = c.ptr(a[4], c.sd, {c.T, c.din});
     const void* W = c.ptr(a[5], c.sd, {c.din, c.dout});
     const float* b = static_cast<float*>(c.ptr(a[6], at::kFloat, {c.dout}));

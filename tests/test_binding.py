@@ -111,3 +111,16 @@ def test_errors_stay_the_binding_s():
     with torch.cuda.stream(s):   # the current stream of the call
         dp.fwd()
     s.synchronize()
+
+
+@pytest.mark.gpu
+def test_function_without_w_down_is_refused_by_the_forward():
+    """The plain layer's W_down has no columns; None has no width, which the forward has to say and not the backward."""
+    import torch
+    x = torch.zeros(4, 64, device="cuda", requires_grad=True)
+    W = torch.zeros(64, 64, device="cuda")
+    with pytest.raises(AttributeError):
+        noble.NobleLinearFunction.apply(x, W, None, *(None,) * 7)
+    y = noble.NobleLinearFunction.apply(x, W, None, W.new_empty(64, 0), *(None,) * 5, W.new_empty(0, 64))
+    y.sum().backward()
+    assert x.grad.shape == x.shape
