@@ -715,15 +715,15 @@ noble_status launch_dense(const Batch<DenseBatch>& bt, TileId tile, hipStream_t 
         const dim3 grid(bt.blocks);
         switch (tile) {
             case kTile256x128:
-                return launch(gemm_tile_kernel<true, BKM, 4, 2, 2, 2, 3, false, B>, grid, dim3(512), st, bt.b);
+                return launch(gemm_tile_kernel<BKM, 4, 2, 2, 2, 3, B>, grid, dim3(512), st, bt.b);
             case kTile128:
-                return launch(gemm_tile_kernel<true, BKM, 2, 2, 2, 2, 3, false, B>, grid, dim3(256), st, bt.b);
+                return launch(gemm_tile_kernel<BKM, 2, 2, 2, 2, 3, B>, grid, dim3(256), st, bt.b);
             case kTile64x128:
-                return launch(gemm_tile_kernel<true, BKM, 2, 2, 1, 2, 3, false, B>, grid, dim3(256), st, bt.b);
+                return launch(gemm_tile_kernel<BKM, 2, 2, 1, 2, 3, B>, grid, dim3(256), st, bt.b);
             case kTile32x128:
                 // seven stages: a few tokens only wait for W, 96 KB of it in flight per CU
                 if constexpr (!BKM)
-                    return launch(gemm_tile_kernel<true, false, 1, 4, 1, 1, 7, false, B>, grid, dim3(256), st, bt.b);
+                    return launch(gemm_tile_kernel<false, 1, 4, 1, 1, 7, B>, grid, dim3(256), st, bt.b);
                 break;
             default: break;
         }

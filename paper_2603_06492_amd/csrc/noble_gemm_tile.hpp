@@ -118,13 +118,15 @@ struct TileFrag {
     }
 };
 
-// WM x WN waves of 32 TM x 32 TN outputs; NST LDS stages of 64-element chunks.
-template <bool AK, bool BKM, int WM, int WN, int TM, int TN, int NST, bool HAS_BSUM, typename Batch>
+// A K-major, B K-major (BKM) or MN-major; WM x WN waves of 32 TM x 32 TN
+// outputs; NST LDS stages of 64-element chunks.
+template <bool BKM, int WM, int WN, int TM, int TN, int NST, typename Batch>
 __global__ __launch_bounds__(64 * WM * WN, (160 * 1024 / (NST * 32 * (WM * TM + WN * TN) * 128)) * WM * WN / 4)
 void gemm_tile_kernel(Batch batch) {
     constexpr int NW = WM * WN, WTM = 32 * TM, WTN = 32 * TN, BM = WM * WTM, BN = WN * WTN;
     constexpr int TA = BM * 128, STAGE = (BM + BN) * 128;
-    using DA = TileDma<AK, BM, NW>;
+    static_assert(NST >= 3, "the loads of a chunk span two others");
+    using DA = TileDma<true, BM, NW>;
     using DB = TileDma<BKM, BN, NW>;
     constexpr int kLoads = DA::PER + DB::PER;
     __shared__ __attribute__((aligned(1024))) char lds[NST * STAGE];
@@ -166,13 +168,8 @@ void gemm_tile_kernel(Batch batch) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    const bool do_bsum = HAS_BSUM && (P.bsum != nullptr) && wm0 == 0;
-    float bs[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bs[j] = 0.f;
-
     if (n > 0) {
-        const TileFrag<AK, BM, TM> fa(wm0, lane);
+        const TileFrag<true, BM, TM> fa(wm0, lane);
         const TileFrag<BKM, BN, TN> fb(wn0, lane);
         const Operand opA = P.A, opB = P.B;
         DA da;
@@ -201,9 +198,8 @@ void gemm_tile_kernel(Batch batch) {
         };
         // Instructions [part_lo(p), part_lo(p + 1)) are part p of a chunk.
         // Part 0 goes out in the last K step of a chunk, parts 1 .. 3 in the
-        // first three of the next: with two stages the load must be early.
-        constexpr int kParts = NST == 2 ? 2 : 4;
-        auto part_lo = [](int p) constexpr { return p >= kParts ? kLoads : kLoads * p / kParts; };
+        // first three of the next.
+        auto part_lo = [](int p) constexpr { return kLoads * p / 4; };
 
 #pragma unroll
         for (int i = 0; i < NST - 1; ++i) {
@@ -226,8 +222,7 @@ void gemm_tile_kernel(Batch batch) {
         int st = 0;   // stage of the chunk being multiplied
         // One K step: MFMAs on fragments cb while the next step's fragments
         // (from stage rs, step s2) and part p of the loads (into stage ds) go out.
-        auto step = [&](int cb, int rs, int s2, int p, int ds, auto bs_c) __attribute__((always_inline)) {
-            constexpr bool BS = decltype(bs_c)::value;
+        auto step = [&](int cb, int rs, int s2, int p, int ds) __attribute__((always_inline)) {
             constexpr int NM = TM * TN, NR = TM + TN;
             const int nb = cb ^ 1;
             const char* ra = lds + rs * STAGE;
@@ -248,18 +243,12 @@ void gemm_tile_kernel(Batch batch) {
                 for (int d = nd * m / NM; d < nd * (m + 1) / NM; ++d) dma(d0 + d, ds);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if constexpr (BS) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) bs[j] += bf2f(b[cb][j][w] & 0xffffu) + bf2f(b[cb][j][w] >> 16);
-            }
         };
-        auto chunk = [&](int i, auto bs_c) __attribute__((always_inline)) {
+        auto chunk = [&](int i) __attribute__((always_inline)) {
             const int prv = st == 0 ? NST - 1 : st - 1, nxt = st + 1 == NST ? 0 : st + 1;
-            step(0, st, 1, 1, prv, bs_c);
-            step(1, st, 2, 2, prv, bs_c);
-            step(0, st, 3, 3, prv, bs_c);
+            step(0, st, 1, 1, prv);
+            step(1, st, 2, 2, prv);
+            step(0, st, 3, 3, prv);
             // Chunk i + 1 has landed once only the later chunks' loads are
             // outstanding; this wave's reads of chunk i are done (lgkmcnt).
             __builtin_amdgcn_sched_barrier(0);
@@ -267,34 +256,16 @@ void gemm_tile_kernel(Batch batch) {
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
             aim(i + NST);
-            step(1, nxt, 0, 0, st, bs_c);
+            step(1, nxt, 0, 0, st);
             st = nxt;
         };
-        auto run_range = [&](int lo, int hi, auto bs_c) __attribute__((always_inline)) {
-            for (int i = lo; i < hi; ++i) chunk(i, bs_c);
+        // A function of its bounds: with the loop written out here, the compiler
+        // computes the offsets of the loads of a K-major B in vector registers.
+        auto run = [&](int lo, int hi) __attribute__((always_inline)) {
+            for (int i = lo; i < hi; ++i) chunk(i);
         };
-        if constexpr (HAS_BSUM) {
-            if (do_bsum) {
-                const int sb = (int)((int64_t)n * tm / P.tiles_m), se = (int)((int64_t)n * (tm + 1) / P.tiles_m);
-                run_range(0, sb, std::false_type{});
-                run_range(sb, se, std::true_type{});
-                run_range(se, n, std::false_type{});
-            } else {
-                run_range(0, n, std::false_type{});
-            }
-        } else {
-            run_range(0, n, std::false_type{});
-        }
+        run(0, n);
         wait_vmcnt<0>();   // no load may reach LDS after the workgroup's end
-    }
-
-    if (do_bsum) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const float s = bs[j] + __shfl_xor(bs[j], 32);
-            const int col = n0 + wn0 + 32 * j + r32;
-            if (h == 0 && col < P.N) unsafeAtomicAdd(P.bsum + col, s);
-        }
     }
 
     const bool add_bias = (P.bias != nullptr) && piece == 0;
