@@ -4,12 +4,16 @@ launch rules choose, and that every launch can be made."""
 
 import os
 import random
+import re
 import shutil
 import subprocess
 
 import pytest
 
 from paper_2603_06492_amd import noble
+
+import test_split_forward_gpu as split
+import test_tiles_gpu as tiles
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_2603_06492_amd")
@@ -120,3 +124,54 @@ def test_unused_gradients_are_cleared_in_their_own_size(record, act, G, r):
         assert st == 0 and launches
         assert zeros["dM"] == G * r * r * size[call[0], call[5]], call
         assert zeros["domega2"] == zeros["dphi2"] == G * r * 4, call
+
+
+def _tile(kernel):
+    """"256x128" of a product kernel's name, None of any other kernel's."""
+    m = re.search(r"gemm_tile_kernel<\w+, (\d+), (\d+), (\d+), (\d+),", kernel)
+    if m:
+        wm, wn, tm, tn = map(int, m.groups())
+        return f"{32 * wm * tm}x{32 * wn * tn}"
+    m = re.search(r"noble::gemm_kernel<float, (\d+), (\d+),", kernel)
+    if m:
+        return f"{m[1]}x{m[2]}"
+    return "256x256" if "gemm_bf16_kernel" in kernel else "64x64" if "gemm_f32_kernel" in kernel else None
+
+
+def _tiles(launches):
+    return [t for t in (_tile(x[3]) for x in launches) if t]
+
+
+@pytest.mark.parametrize("case", tiles.CASES, ids=[c[0] for c in tiles.CASES])
+def test_tile_cases_run_their_tiles(record, case):
+    name, T, di, do, r, G = case
+    y, b = (_tiles(x[1]) for x in record([(c, T, di, do, r, "bf16", "cosnet", G) for c in ("fwd", "bwd")]))
+    assert (y, b[:-1]) == tiles.TILES[name]   # the backward's last product: the weight gradients
+
+
+@pytest.mark.parametrize("case", tiles.F32_CASES, ids=[c[0] for c in tiles.F32_CASES])
+def test_float32_tile_cases_run_their_tiles(record, case):
+    name, T, di, do, r, G = case
+    y, b = (_tiles(x[1]) for x in record([(c, T, di, do, r, "f32", "cosnet", G) for c in ("fwd", "bwd")]))
+    assert (*y, *b) == tiles.F32_TILES[name]
+
+
+@pytest.mark.parametrize("case", split.CASES + split.CASES3, ids=[c[0] for c in split.CASES + split.CASES3])
+def test_split_cases_run_their_forms(record, case):
+    name, T, di, do, r, G = case
+    three = case in split.CASES3
+    tile, pieces, finish = (split.FORMS3 if three else split.FORMS)[name]
+    act = "cosnet3" if three else "cosnet"
+    full, static, least = record([
+        ("fwd", T, di, do, r, "bf16", act, G), ("static", T, di, do, r, "bf16", act, G),
+        ("fwd", T, di, do, r, "bf16", act, G, split._unsplit_scratch(T, di, do, r, G))])
+    assert full == static   # the static scratch always holds the split form
+    launches = full[1]
+    assert _tiles(launches) == [tile]
+    bm, bn = map(int, tile.split("x"))
+    cdiv = lambda a, b: -(-a // b)
+    assert launches[0][0] == pieces * cdiv(T, bm) * (cdiv(do, bn) + cdiv(G * r, bn))
+    m = re.search(r"noble::(y_finish|chain_finish)_kernel(<\d>)?", launches[-1][3])
+    assert m[1] + (m[2] or "") == finish
+    assert len(launches) == (2 if finish == "chain_finish" else 3)
+    assert "proj_kernel" in least[1][0][3]   # the least scratch: the unsplit form
