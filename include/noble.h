@@ -144,9 +144,12 @@ noble_status noble_linear_workspace_size(const noble_linear_desc* desc,
  * noble_linear_workspace_size, which covers both calls): a forward-only or
  * inference caller may pass a buffer of this size to noble_linear_fwd.
  * Same errors as noble_linear_workspace_size; makes no HIP call.  A layer of
- * few tokens runs faster with this much; the forward accepts any buffer that
- * holds the bf16 branch output [T, R] and the float32 partials of x W_down
- * that the unsplit form uses. */
+ * few tokens runs faster with this much: x W and x W_down are then summed in
+ * pieces of d_in.  The forward accepts any buffer that holds the bf16 branch
+ * output [T, R] and the float32 partials of x W_down that the unsplit form
+ * uses, and with less than this runs that form.  The two forms' y and H differ
+ * by the float32 rounding of those sums: with W_up = 0 the unsplit form's y
+ * equals the plain layer's bit for bit, one of several pieces to rounding. */
 noble_status noble_linear_fwd_scratch_size(const noble_linear_desc* desc,
                                            size_t* scratch_bytes);
 
@@ -179,7 +182,8 @@ noble_status noble_linear_fwd(const noble_linear_desc* desc,
  * device memory: NOBLE_STATIC_SCRATCH_BYTES on each GPU it runs on, from the
  * first call on that GPU until the process ends.  It allocates nothing and
  * makes no allocating call.  Arguments, outputs and status codes are those of
- * noble_linear_fwd; a layer whose forward needs more scratch than the array
+ * noble_linear_fwd (y and H bit for bit those it gives with a scratch of
+ * noble_linear_fwd_scratch_size bytes); a layer whose forward needs more scratch than the array
  * holds (noble_linear_fwd_scratch_size above NOBLE_STATIC_SCRATCH_BYTES;
  * at r = 128 that is beyond about 87000 tokens) returns
  * NOBLE_ERR_WORKSPACE_TOO_SMALL before any HIP call.  Every call on one GPU

@@ -362,12 +362,14 @@ TileId pick_tile(int64_t G, int64_t M, int64_t N, int nk) {
 // read four partials in one round trip, so each further four cost 2.1 us: 6 to
 // 12 pieces pay only where a long K meets few tiles (1 x 8192 -> 2048: 4 pieces
 // 27.2 us, 8 23.2).  At least four K chunks per piece, as in the rank
-// projection (shorter pieces gained 2% at most).  Measured over 41 shapes of 1 to 2048 tokens
+// projection (shorter pieces gained 2% at most).  Measured over 45 shapes of 1 to 2048 tokens
 // (cold weights, us, unsplit / split): 1 x 2048 -> 6144 37.8 / 22.7,
 // 16 x 2048 -> 8192 37.8 / 24.8, 777 x 8192 -> 2048 94 / 60, 1600 x 4096 ->
 // 768 64 / 40, 2048 x 4096 -> 1024 55 / 44; at the line 700 x 1024 -> 3072
-// 31.4 / 32.7 and 1100 x 512 -> 1536 29.2 / 31.5 (unsplit taken).  The rule's
-// choice is on average 1% off the best of the 13 forms measured.
+// 31.4 / 32.7 and 1100 x 512 -> 1536 29.2 / 31.5 (unsplit taken).  Where the
+// rule's choice was among the forms measured (38 of the shapes) it is 1.5% off
+// the best of them on average, and most where the static scratch bars the split
+// (2048 x 8192 -> 6144: 269 unsplit, 242 in three pieces).
 // The layout never exceeds the static scratch, so that noble_linear_fwd_static
 // and noble_linear_fwd take the same form.
 struct FwdPlan {
@@ -548,11 +550,14 @@ int choose_split_partials(int tiles, int nk, int64_t MN, int64_t cap) {
     return bs;
 }
 
-// K splits of the weight-gradient launch (K = T tokens).  The pieces of
-// every product (dW, and the rank products dW_down, dW_up, dM) store float32
-// partials that reduce_kernel sums in piece order.  Float atomics were used
-// for the rank products before: they are device-scope, so the eight XCDs'
-// adds meet beyond their L2s, and they cost about 1 MB of output per us.
+// K splits of the weight-gradient launch (K = T tokens).  The float32 path uses
+// the same model, with the bf16 kernel's constants and 128 x 128 tiles, also
+// where the launch then runs 64 x 64 ones (f32_tile sees the splits chosen
+// here): there it only orders the splits roughly.  The pieces of every product
+// (dW, and the rank products dW_down, dW_up, dM) store float32 partials that
+// reduce_kernel sums in piece order.  Float atomics were used for the rank
+// products before: they are device-scope, so the eight XCDs' adds meet beyond
+// their L2s, and they cost about 1 MB of output per us.
 //  - r = 0: dW alone, choose_split_partials.
 //  - r > 0: both splits together (the rank problems share dW's launch and
 //    can fill the CUs that a smaller dW split leaves), minimising the

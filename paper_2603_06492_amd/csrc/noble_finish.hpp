@@ -6,11 +6,11 @@
 // the branch), then the chain, then this kernel: a layer of few tokens has
 // too few output tiles to keep 256 CUs reading W, and its K loop is split
 // over the idle ones.  Bound by bytes (S T d_out 4 of partials, which the
-// preceding launches left in the memory-side cache) and, for a few tokens, by
-// the latency of one round trip: every load is issued before any is waited
-// for.  32 tokens x 128 columns per workgroup, one 32 x 32 block per wave;
-// W_up's [r][128] tile goes through LDS (transposing reads), C2's fragments
-// straight to registers.
+// products store non-temporal, as they do y and dx) and, for a few tokens, by
+// the latency of one round trip: the loads of four partials are issued before
+// any is waited for.  32 tokens x 128 columns per workgroup, one 32 x 32 block
+// per wave; W_up's [r][128] tile goes through LDS (transposing reads), C2's
+// fragments straight to registers.
 #pragma once
 
 #include "noble_gemm_tile.hpp"

@@ -1,12 +1,13 @@
 // float32 grouped MFMA GEMM on 64 x 64 tiles with direct-to-LDS loads.
 //
-// For launches of less than a wave of gemm_kernel's 128 x 128 tiles.  Bound by
-// the float32 MFMAs (a chunk is 0.43 us of them at full clock) where its tiles
-// fill the CUs, and by the last CU's tiles otherwise: hence small tiles, and
-// three LDS stages (48 KB) so that three workgroups share a CU.  Against
-// register staging on the same tile, forward / backward (us): 2048 x 768 ->
-// 768 62.3 / 101.5 -> 58.7 / 98.8, 64 x 1024 -> 1024 63.0 / 68.9 -> 56.2 / 67.8,
-// 2048 x 1024 -> 1024 86.2 / 147.2 -> 82.0 / 146.7.
+// For launches that gemm_kernel's 128 x 128 tiles would leave CUs idle in (the
+// rule is f32_tile's).  Bound by the float32 MFMAs (a chunk is 0.43 us of them
+// at full clock) where its tiles fill the CUs, and by the last CU's tiles
+// otherwise: hence small tiles, and three LDS stages (48 KB) so that three
+// workgroups share a CU.  Against register staging on the same tile, forward /
+// backward (us): 2048 x 768 -> 768 62.3 / 101.5 -> 58.7 / 98.8, 64 x 1024 ->
+// 1024 63.0 / 68.9 -> 56.2 / 67.8, 2048 x 1024 -> 1024 86.2 / 147.2 -> 82.0 /
+// 146.7.
 //
 // Operands keep their HBM orientation in LDS:
 //  - K-major: [64 rows][128 B], 16-byte chunk c of row q at c ^ ((q ^ q/8) & 7);

@@ -1,7 +1,7 @@
 """noble_linear_fwd_static (the forward on the library's static device
 scratch, for callers that cannot allocate) against noble_linear_fwd on the
-same inputs: y and the reserve H bit for bit, on two calls in a row whose
-second is smaller (the array keeps the first call's contents)."""
+same inputs: y and the reserve H bit for bit, on calls in a row (the array
+keeps the contents of the earlier, larger ones)."""
 
 import numpy as np
 import pytest
@@ -16,6 +16,8 @@ CASES = [
     ("bf16_r128_T2500", 2500, 512, 384, 128, 1, "bf16", "cosnet"),
     ("bf16_g3_r40_T300", 300, 200, 264, 40, 3, "bf16", "gelu_m"),
     ("f32_r24_T333", 333, 96, 136, 24, 1, "f32", "cosnet"),
+    # split over K: as noble_linear_fwd with the scratch that the size query gives
+    ("bf16_r136_T33_split", 33, 2056, 1000, 136, 1, "bf16", "cosnet"),
 ]
 
 
