@@ -55,7 +55,7 @@ def branch_floor(d_in, d_out, r, mixing=1, groups=1):
 
 
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "wgrad_ffn_up_T32768_traffic.md")
-WGRAD_KERNEL = "noble::gemm_bf16_kernel<false, false, true, 0>"
+WGRAD_KERNEL = "noble::gemm_bf16_kernel<false, false, true, 0, noble::GemmBatchN<14> >"
 
 
 # Sources of the roofline kernel (gemm_bf16_kernel): a traffic record stays

@@ -2,6 +2,7 @@
 tests/c/launch_record.cpp (HIP's launch function replaced, no GPU): what the
 launch rules choose, and that every launch can be made."""
 
+import json
 import os
 import random
 import re
@@ -12,6 +13,7 @@ import pytest
 
 from paper_2603_06492_amd import noble
 
+import bench
 import test_split_forward_gpu as split
 import test_tiles_gpu as tiles
 
@@ -175,3 +177,12 @@ def test_split_cases_run_their_forms(record, case):
     assert m[1] + (m[2] or "") == finish
     assert len(launches) == (2 if finish == "chain_finish" else 3)
     assert "proj_kernel" in least[1][0][3]   # the least scratch: the unsplit form
+
+
+def test_bench_names_the_kernel_it_reports(record):
+    """The roofline entry's launch: the FFN-up projection's weight gradients, in the workgroups of the traffic record."""
+    _, launches, _ = record([("bwd", 32768, 2048, 8192, 128, "bf16", "cosnet", 1)])[0]
+    with open(bench.TRAFFIC_RECORD) as fh:
+        rec = json.loads(re.search(r"^traffic_record: (\{.*\})$", fh.read(), re.M)[1])
+    assert rec["kernel"] == bench.WGRAD_KERNEL
+    assert [x[0] for x in launches if x[3].startswith(f"void {bench.WGRAD_KERNEL}(")] == [rec["workgroups"]]
